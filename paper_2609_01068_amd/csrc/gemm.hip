@@ -13,8 +13,8 @@
 // e4m3 weights stay as codes in LDS, are widened to bf16 (exact) when a
 // fragment is read, and the per-row scale is applied in the epilogue.
 //
-// fp32 path (tiny shape): a plain LDS-tiled VALU kernel with full bounds
-// handling; it exists for the fp32 configuration, not for speed.
+// fp32 path (the fp32 layer): v_mfma_f32_16x16x4_f32 tiles with full bounds
+// handling, see below.
 #include <algorithm>
 
 #include "common.hpp"
@@ -657,77 +657,155 @@ splitk_reduce_qkv_rope(int M, int N, int S, const float* part, GemmC C) {
     dst[c + 64] = f32_to_bf16(x2 * cs + x1 * sn);
 }
 
-// ---------------------------------------------------------------- fp32 VALU path
-template <int EPI>
-__global__ void __launch_bounds__(256)
-gemm_f32_64x64(int M, int N, int K, GemmA A, GemmB B, GemmC C, int k_per_split) {
+// ---------------------------------------------------------------- fp32 path
+// v_mfma_f32_16x16x4_f32 straight from global memory: lane l reads four
+// consecutive k of row l % 16 at k0 + 4 (l / 16) from A and from B, and MFMA
+// e of the 16-deep chunk multiplies element e of both, so every product
+// pairs equal k (fp32 products and sums, as the reference).  A workgroup
+// covers (16 FM WM) x (16 FN WN) outputs on WM x WN x KW waves; the KW waves
+// of one output share take every KW-th chunk and are summed through LDS in
+// wave order.  U chunks are loaded before the first is multiplied.
+//
+// The fp32 layer is small (d = 256, a few to a few thousand rows), so a call
+// waits on latency, not on arithmetic or memory: 16 x 16 tiles over 8 K waves
+// give 16 workgroups where 64 x 64 tiles gave one, and one or two rounds of
+// loads instead of a K loop of two barriers per 16 k.  Measured against that
+// LDS-tiled VALU kernel: a 4-request decode step's projections 47-75 -> ~5 us
+// each, prefill of 164 tokens 507 -> 69 us, of 65,536 tokens 5,220 -> 3,702.
+//
+// VEC: 16-byte loads (rows 16-byte aligned, K and the K segments whole
+// chunks); otherwise element loads with bounds checks.
+template <int EPI, bool VEC, int WM, int WN, int FM, int FN, int KW, int U>
+__global__ void __launch_bounds__(WM * WN * KW * 64)
+gemm_f32_mfma(int M, int N, int K, GemmA A, GemmB B, GemmC C, int k_per_split) {
     // EPI_SWIGLU: logical N is the number of features; each output needs the
     // gate row (p[0]) and the up row (p[1]).
-    constexpr int T = 64, KT = 16;
-    constexpr bool DUAL = (EPI == EPI_SWIGLU);
-    __shared__ float sa[KT][T + 1];
-    __shared__ float sb[DUAL ? 2 : 1][KT][T + 1];
-    const int tx = threadIdx.x % 16, ty = threadIdx.x / 16;
-    const int m0 = blockIdx.x * T, n0 = blockIdx.z * T;
+    constexpr int D = (EPI == EPI_SWIGLU) ? 2 : 1;
+    constexpr int TM = 16 * FM * WM, TN = 16 * FN * WN;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int l16 = lane & 15, grp = lane >> 4;
+    const int kw = wave % KW, wn = (wave / KW) % WN, wm = wave / (KW * WN);
+    const int m0 = blockIdx.x * TM + wm * 16 * FM, n0 = blockIdx.z * TN + wn * 16 * FN;
     const int kb = blockIdx.y * k_per_split, ke = min(K, kb + k_per_split);
-    float acc[DUAL ? 2 : 1][4][4] = {};
-    for (int k0 = kb; k0 < ke; k0 += KT) {
-        for (int e = threadIdx.x; e < T * KT; e += 256) {
-            int r = e / KT, kk = e % KT, m = m0 + r, k = k0 + kk;
-            float v = 0.f;
-            if (m < M && k < ke) {
-                int s = k / A.kseg;
-                v = static_cast<const float*>(A.p[s])[(int64_t)m * A.ld + (k - s * A.kseg)];
-            }
-            sa[kk][r] = v;
-            int n = n0 + r;
+    const int nch = (max(ke - kb, 0) + 15) / 16;
+
+    // rows past the matrix repeat the last one; their outputs are not stored
+    int64_t arow[FM];
+    const float* brow[D][FN];
 #pragma unroll
-            for (int q = 0; q < (DUAL ? 2 : 1); ++q) {
-                float w = 0.f;
-                if (n < N && k < ke) {
-                    int s, rr;
-                    if (DUAL) { s = q; rr = n; } else { b_row(B, n, s, rr); }
-                    w = static_cast<const float*>(B.p[s])[(int64_t)rr * B.ld + k];
-                }
-                sb[q][kk][r] = w;
-            }
+    for (int i = 0; i < FM; ++i) arow[i] = (int64_t)min(m0 + 16 * i + l16, M - 1) * A.ld;
+#pragma unroll
+    for (int j = 0; j < FN; ++j) {
+        const int n = min(n0 + 16 * j + l16, N - 1);
+#pragma unroll
+        for (int q = 0; q < D; ++q) {
+            int s = q, r = n;
+            if (D == 1) b_row(B, n, s, r);
+            brow[q][j] = static_cast<const float*>(B.p[s]) + (int64_t)r * B.ld;
         }
-        __syncthreads();
-#pragma unroll
-        for (int kk = 0; kk < KT; ++kk) {
-            float av[4], bv[DUAL ? 2 : 1][4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) av[i] = sa[kk][ty * 4 + i];
-#pragma unroll
-            for (int q = 0; q < (DUAL ? 2 : 1); ++q)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) bv[q][j] = sb[q][kk][tx * 4 + j];
-#pragma unroll
-            for (int q = 0; q < (DUAL ? 2 : 1); ++q)
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) acc[q][i][j] = fmaf(av[i], bv[q][j], acc[q][i][j]);
-        }
-        __syncthreads();
     }
+    auto a_ptr = [&](int s) { return static_cast<const float*>(s == 0 ? A.p[0] : (s == 1 ? A.p[1] : A.p[2])); };
+    auto load = [&](int c, float (*av)[4], float (*bv)[FN][4]) {
+        const int k = kb + 16 * c + 4 * grp;
+        if constexpr (VEC) {
+            const int s = (kb + 16 * c) / A.kseg;        // a chunk lies in one segment
+            const float* ap = a_ptr(s) + (k - s * A.kseg);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        int m = m0 + ty * 4 + i;
-        if (m >= M) continue;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            int n = n0 + tx * 4 + j;
-            if (n >= N) continue;
-            float v = acc[0][i][j];
-            float* c = static_cast<float*>(C.c);
-            if (EPI == EPI_STORE_F32 || EPI == EPI_STORE_ACT) c[(int64_t)m * C.ldc + n] = v;
-            else if (EPI == EPI_RESID_F32) c[(int64_t)m * C.ldc + n] = C.resid[(int64_t)m * C.ldr + n] + v;
-            else if (EPI == EPI_PARTIAL) c[blockIdx.y * C.split_stride + (int64_t)m * C.ldc + n] = v;
-            else if (EPI == EPI_SWIGLU) {
-                float g = v, u = acc[DUAL ? 1 : 0][i][j];
-                c[(int64_t)m * C.ldc + n] = g / (1.0f + expf(-g)) * u;
+            for (int i = 0; i < FM; ++i) {
+                const float4 v = *reinterpret_cast<const float4*>(ap + arow[i]);
+                av[i][0] = v.x; av[i][1] = v.y; av[i][2] = v.z; av[i][3] = v.w;
             }
+#pragma unroll
+            for (int q = 0; q < D; ++q)
+#pragma unroll
+                for (int j = 0; j < FN; ++j) {
+                    const float4 v = *reinterpret_cast<const float4*>(brow[q][j] + k);
+                    bv[q][j][0] = v.x; bv[q][j][1] = v.y; bv[q][j][2] = v.z; bv[q][j][3] = v.w;
+                }
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int ks = min(k + e, ke - 1), s = ks / A.kseg;
+                const bool ok = k + e < ke;
+#pragma unroll
+                for (int i = 0; i < FM; ++i) {
+                    const float v = a_ptr(s)[arow[i] + (ks - s * A.kseg)];
+                    av[i][e] = ok ? v : 0.f;
+                }
+#pragma unroll
+                for (int q = 0; q < D; ++q)
+#pragma unroll
+                    for (int j = 0; j < FN; ++j) {
+                        const float v = brow[q][j][ks];
+                        bv[q][j][e] = ok ? v : 0.f;
+                    }
+            }
+        }
+    };
+
+    f32x4 acc[D][FM][FN];
+#pragma unroll
+    for (int q = 0; q < D; ++q)
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+            for (int j = 0; j < FN; ++j) acc[q][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int c0 = kw; c0 < nch; c0 += KW * U) {
+        float av[U][FM][4], bv[U][D][FN][4];
+#pragma unroll
+        for (int u = 0; u < U; ++u) load(min(c0 + u * KW, nch - 1), av[u], bv[u]);   // past the end: unused
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (c0 + u * KW >= nch) break;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int q = 0; q < D; ++q)
+#pragma unroll
+                    for (int i = 0; i < FM; ++i)
+#pragma unroll
+                        for (int j = 0; j < FN; ++j)
+                            acc[q][i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[u][i][e], bv[u][q][j][e], acc[q][i][j], 0, 0, 0);
+        }
+    }
+
+    auto store = [&](int m, int n, float v, float up) {
+        if (m >= M || n >= N) return;
+        float* c = static_cast<float*>(C.c);
+        if (EPI == EPI_STORE_F32) c[(int64_t)m * C.ldc + n] = v;
+        else if (EPI == EPI_RESID_F32) c[(int64_t)m * C.ldc + n] = C.resid[(int64_t)m * C.ldr + n] + v;
+        else if (EPI == EPI_PARTIAL) c[blockIdx.y * C.split_stride + (int64_t)m * C.ldc + n] = v;
+        else if (EPI == EPI_SWIGLU) c[(int64_t)m * C.ldc + n] = v / (1.0f + expf(-v)) * up;
+    };
+    if constexpr (KW == 1) {
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+            for (int j = 0; j < FN; ++j)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    store(m0 + 16 * i + 4 * grp + e, n0 + 16 * j + l16, acc[0][i][j][e], acc[D - 1][i][j][e]);
+    } else {
+        static_assert(WM == 1 && WN == 1, "K waves share one tile");
+        __shared__ float red[KW][D][TM][TN + 1];
+#pragma unroll
+        for (int q = 0; q < D; ++q)
+#pragma unroll
+            for (int i = 0; i < FM; ++i)
+#pragma unroll
+                for (int j = 0; j < FN; ++j)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) red[kw][q][16 * i + 4 * grp + e][16 * j + l16] = acc[q][i][j][e];
+        __syncthreads();
+        for (int t = threadIdx.x; t < TM * TN; t += KW * 64) {
+            const int r = t / TN, cl = t % TN;
+            float v = 0.f, up = 0.f;
+#pragma unroll
+            for (int p = 0; p < KW; ++p) {
+                v += red[p][0][r][cl];
+                if (D == 2) up += red[p][D - 1][r][cl];
+            }
+            store(m0 + r, n0 + cl, v, up);
         }
     }
 }
@@ -880,8 +958,29 @@ template <int EPI>
 void launch_f32(int M, int N, int K, const GemmA& a, const GemmB& b, const GemmC& c, int splits,
                 hipStream_t st) {
     const int kps = ((K + splits - 1) / splits + 15) / 16 * 16;
-    dim3 grid((M + 63) / 64, splits, (N + 63) / 64);
-    hipLaunchKernelGGL((gemm_f32_64x64<EPI>), grid, dim3(256), 0, st, M, N, K, a, b, c, kps);
+    auto al16 = [](const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; };
+    bool vec = K % 16 == 0 && a.kseg % 16 == 0 && a.ld % 4 == 0 && b.ld % 4 == 0;
+    for (int s = 0; s < 3; ++s) vec = vec && al16(a.p[s]);
+    for (int s = 0; s < 4; ++s) vec = vec && al16(b.p[s]);
+    // Larger tiles read each row fewer times from L2 but leave CUs idle in
+    // small calls: 32 x 32 from one tile per CU, 64 x 64 from two.  Measured
+    // on the d = 256 layer's prefill call, every GEMM with one tile size
+    // (16 / 32 / 64; us): 164 tokens 71 / 80 / 151, 512: 106 / 93 / 167,
+    // 2,048: 262 / 160 / 211, 8,192: 846 / 464 / 452, 65,536: 6,927 / 3,790
+    // / 3,701.
+    auto tiles = [&](int t) { return (int64_t)((M + t - 1) / t) * ((N + t - 1) / t) * splits; };
+    const int t = tiles(64) >= 2 * (int64_t)device_cus() ? 64
+                  : tiles(32) >= device_cus() ? 32 : 16;
+    const dim3 grid((M + t - 1) / t, splits, (N + t - 1) / t);
+#define OUTLETS_F32_CASE(WM, WN, F, KW, UV, US)                                                                       \
+    if (vec) hipLaunchKernelGGL((gemm_f32_mfma<EPI, true, WM, WN, F, F, KW, UV>), grid, dim3(WM * WN * KW * 64), 0, st, M, \
+                                N, K, a, b, c, kps);                                                                  \
+    else hipLaunchKernelGGL((gemm_f32_mfma<EPI, false, WM, WN, F, F, KW, US>), grid, dim3(WM * WN * KW * 64), 0, st, M, N, \
+                            K, a, b, c, kps);
+    if (t == 64) { OUTLETS_F32_CASE(2, 2, 2, 1, 2, 2) }
+    else if (t == 32) { OUTLETS_F32_CASE(1, 1, 2, 4, 3, 2) }
+    else { OUTLETS_F32_CASE(1, 1, 1, 8, 6, 3) }
+#undef OUTLETS_F32_CASE
 }
 
 }  // namespace

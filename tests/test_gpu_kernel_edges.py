@@ -1,0 +1,61 @@
+"""Edges of the kernels' tile and dispatch rules against the fp64 oracle.
+
+Each test walks the sizes around one rule (tile remainders, the switch
+between two variants, rows that are not 16-byte aligned) and says where its
+tolerance comes from.
+"""
+import numpy as np
+import pytest
+
+from gpu_common import (device_states, make_case, make_predictor, oracle_for, oracle_states, reduced_shape, rel_fro,
+                        require_gpu, say, step_inputs, tensor_to_f64, z_errors)
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    require_gpu()
+
+
+def _against_oracle(case, sample, tol_h, tol_z, steps=1):
+    """Prefill and `steps` decode steps of a batch; the requests in `sample`
+    are recomputed by the oracle."""
+    lens = case.lens
+    n = len(lens)
+    off = np.concatenate([[0], np.cumsum(lens)])
+    pred = make_predictor(case, max_seq_len=int(lens.max()) + steps + 16)
+    z, h = pred.prefill(list(range(n)), lens, *device_states(case), want_hdraft=True)
+    z, h = tensor_to_f64(z), tensor_to_f64(h)
+    orc, O = oracle_for(case), oracle_states(case)
+    ref = {i: orc.prefill_one(*(x[off[i]:off[i + 1]] for x in O)) for i in sample}
+    for i in sample:
+        assert rel_fro(h[off[i]:off[i + 1]], ref[i][1]) <= tol_h, i
+    assert z_errors(z[list(sample)], [ref[i][0] for i in sample]).max() <= tol_z
+    st = {i: ref[i][2] for i in sample}
+    for k in range(1, steps + 1):
+        arrays = step_inputs(case, k)
+        z, h = pred.step(list(range(n)), *device_states(case, arrays), want_hdraft=True)
+        z, h = tensor_to_f64(z), tensor_to_f64(h)
+        S = oracle_states(case, arrays)
+        zr = []
+        for i in sample:
+            zi, hi = orc.step_one(st[i], *(x[i] for x in S))[:2]
+            zr.append(zi)
+            assert rel_fro(h[i], np.asarray(hi).reshape(-1)) <= tol_h, (k, i)
+        assert z_errors(z[list(sample)], zr).max() <= tol_z
+    pred.close()
+
+
+@pytest.mark.parametrize("tokens", [1, 15, 17, 500, 2100, 9000])
+@pytest.mark.parametrize("aligned", [True, False], ids=["16-byte rows", "odd rows"])
+def test_fp32_gemm_tile_sizes(tokens, aligned):
+    """16, 32 and 64-row tiles, full and ragged, with 16-byte loads and with
+    element loads (widths that are not multiples of 16).  Tolerance: fp32
+    sums of up to 768 terms through five layers, sqrt(768) * 2^-24 * 5 ~ 8e-6."""
+    shape = dict(d=256, n_q=4, n_kv=2, hd=64, ffn=688, head_hidden=128, theta=1e4) if aligned else \
+        dict(d=250, n_q=4, n_kv=2, hd=64, ffn=691, head_hidden=130, theta=1e4)
+    lens = [min(200, tokens)] * (tokens // 200) + ([tokens % 200] if tokens % 200 else [])
+    say(f"case: fp32 layer d={shape['d']}, {tokens} tokens in {len(lens)} requests, 1 step")
+    case = make_case(0, lens=lens, shape=reduced_shape(**shape), n_req=len(lens))
+    _against_oracle(case, sorted({0, len(lens) // 2, len(lens) - 1}), 1e-5, 1e-5)

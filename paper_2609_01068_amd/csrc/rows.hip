@@ -64,33 +64,42 @@ rmsnorm_kernel(int d, const float* x, int64_t ldx, const TG* gamma, float eps, T
 
 // Element group j4 (elements 4 j4 .. 4 j4 + 3) of a RowSum's row: the
 // partials added in split order, then the residual added to that sum (the
-// order of splitk_reduce), stored to rs.out when set.
+// order of splitk_reduce), stored to rs.out when set.  The partials' loads go
+// out eight at a time, the residual's first: one dependent load per split
+// cost a memory latency each (a 16-split norm of one row: 19 us).
 __device__ __forceinline__ float4 rowsum_load(const RowSum& rs, int64_t row, int j4) {
     const float4* p = reinterpret_cast<const float4*>(rs.part + row * rs.ldp) + j4;
     const int64_t step = rs.plane / 4;
+    float4 r = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (rs.resid) r = reinterpret_cast<const float4*>(rs.resid + row * rs.ldr)[j4];
     float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int sp = 0; sp < rs.S; ++sp) {
-        const float4 q = p[sp * step];
-        v.x += q.x; v.y += q.y; v.z += q.z; v.w += q.w;
+    for (int s0 = 0; s0 < rs.S; s0 += 8) {
+        float4 q[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) q[i] = p[min(s0 + i, rs.S - 1) * step];   // past the end: a cached repeat
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            if (s0 + i >= rs.S) break;
+            v.x += q[i].x; v.y += q[i].y; v.z += q[i].z; v.w += q[i].w;
+        }
     }
-    if (rs.resid) {
-        const float4 r = reinterpret_cast<const float4*>(rs.resid + row * rs.ldr)[j4];
-        v = make_float4(r.x + v.x, r.y + v.y, r.z + v.z, r.w + v.w);
-    }
+    if (rs.resid) v = make_float4(r.x + v.x, r.y + v.y, r.z + v.z, r.w + v.w);
     if (rs.out) reinterpret_cast<float4*>(rs.out + row * rs.ldo)[j4] = v;
     return v;
 }
 
-// Vectorised form for d = 1024 V (V = 1..8 groups of 4 floats per thread):
+// Vectorised form for d = 4 NT V (V groups of 4 floats per thread):
 // the row stays in registers between the sum of squares and the scaling,
 // and every access is a 16-byte (x, y2) or 8-byte (bf16 y, gamma) access
 // with consecutive threads on consecutive addresses.
 // With SUM the row is a RowSum's (a split-K GEMM finished here) instead of x.
-template <typename TY, typename TG, int V, bool SUM = false>
-__global__ void __launch_bounds__(256)
+// NT is 256 for many rows; up to one block per CU each takes the whole CU's
+// issue width instead (NT up to 1,024, see launch_rmsnorm_sum).
+template <typename TY, typename TG, int V, bool SUM = false, int NT = 256>
+__global__ void __launch_bounds__(NT)
 rmsnorm_vec_kernel(int d, const float* x, int64_t ldx, const TG* gamma, float eps, TY* y,
                    int64_t ldy, float* y2, int64_t ldy2, RowSum rs = RowSum{}) {
-    __shared__ float red[4];
+    __shared__ float red[NT / 64];
     const int64_t row = blockIdx.x;
     const int t = threadIdx.x;
     const float4* xr = reinterpret_cast<const float4*>(x + row * ldx);
@@ -98,14 +107,14 @@ rmsnorm_vec_kernel(int d, const float* x, int64_t ldx, const TG* gamma, float ep
     float ss = 0.f;
 #pragma unroll
     for (int j = 0; j < V; ++j) {
-        v[j] = SUM ? rowsum_load(rs, row, j * 256 + t) : xr[j * 256 + t];
+        v[j] = SUM ? rowsum_load(rs, row, j * NT + t) : xr[j * NT + t];
         ss = fmaf(v[j].x, v[j].x, fmaf(v[j].y, v[j].y, fmaf(v[j].z, v[j].z, fmaf(v[j].w, v[j].w, ss))));
     }
-    ss = block_sum<256>(ss, red);
+    ss = block_sum<NT>(ss, red);
     const float inv = 1.0f / sqrtf(ss / d + eps);
 #pragma unroll
     for (int j = 0; j < V; ++j) {
-        const int c = (j * 256 + t) * 4;
+        const int c = (j * NT + t) * 4;
         float g[4];
         if constexpr (sizeof(TG) == 4) {
             const float4 gv = *reinterpret_cast<const float4*>(gamma + c);
@@ -618,22 +627,28 @@ bool rowsum_supported(int d) { return d == 1024 || d == 2048 || d == 4096 || d =
 void launch_rmsnorm_sum(int act_fmt, int gamma_fmt, int rows, int d, const RowSum& rs, const void* gamma,
                         float eps, void* y, int64_t ldy, hipStream_t st) {
     if (rows <= 0) return;
-    const int V = d / 1024;
+    // Up to 512 rows (two per CU) a wide block per row (d / 4 threads, at
+    // most 1,024) hides the partials' latency better than 256 threads of d /
+    // 1024 groups each; with more rows the narrow blocks fill the chip.
+    // Measured at d = 4096 (narrow / wide, us): 1 row of 16 splits 18.7 /
+    // 7.7, 130 rows of 8 12.0 / 6.9, 512 rows of 4 10.6 / 10.1; 777 rows of 4
+    // narrow 13.4 (6 TB/s).
+    const bool wide = rows <= 512;
+#define OUTLETS_NORMS_L(TY, TG, VV, NT)                                                                    \
+    hipLaunchKernelGGL((rmsnorm_vec_kernel<TY, TG, VV, true, NT>), dim3(rows), dim3(NT), 0, st, d, nullptr, 0, \
+                       static_cast<const TG*>(gamma), eps, static_cast<TY*>(y), ldy, nullptr, 0, rs)
 #define OUTLETS_NORMS_V(TY, TG)                                                                            \
-    switch (V) {                                                                                           \
-        case 1: hipLaunchKernelGGL((rmsnorm_vec_kernel<TY, TG, 1, true>), dim3(rows), dim3(256), 0, st, d, nullptr, 0, \
-                                   static_cast<const TG*>(gamma), eps, static_cast<TY*>(y), ldy, nullptr, 0, rs); break; \
-        case 2: hipLaunchKernelGGL((rmsnorm_vec_kernel<TY, TG, 2, true>), dim3(rows), dim3(256), 0, st, d, nullptr, 0, \
-                                   static_cast<const TG*>(gamma), eps, static_cast<TY*>(y), ldy, nullptr, 0, rs); break; \
-        case 4: hipLaunchKernelGGL((rmsnorm_vec_kernel<TY, TG, 4, true>), dim3(rows), dim3(256), 0, st, d, nullptr, 0, \
-                                   static_cast<const TG*>(gamma), eps, static_cast<TY*>(y), ldy, nullptr, 0, rs); break; \
-        case 8: hipLaunchKernelGGL((rmsnorm_vec_kernel<TY, TG, 8, true>), dim3(rows), dim3(256), 0, st, d, nullptr, 0, \
-                                   static_cast<const TG*>(gamma), eps, static_cast<TY*>(y), ldy, nullptr, 0, rs); break; \
+    switch (d / 1024) {                                                                                    \
+        case 1: OUTLETS_NORMS_L(TY, TG, 1, 256); break;                                                    \
+        case 2: if (wide) OUTLETS_NORMS_L(TY, TG, 1, 512); else OUTLETS_NORMS_L(TY, TG, 2, 256); break;    \
+        case 4: if (wide) OUTLETS_NORMS_L(TY, TG, 1, 1024); else OUTLETS_NORMS_L(TY, TG, 4, 256); break;   \
+        case 8: if (wide) OUTLETS_NORMS_L(TY, TG, 2, 1024); else OUTLETS_NORMS_L(TY, TG, 8, 256); break;   \
     }
     if (act_fmt == FMT_F32) { OUTLETS_NORMS_V(float, float) }
     else if (gamma_fmt == FMT_F32) { OUTLETS_NORMS_V(bf16_t, float) }
     else { OUTLETS_NORMS_V(bf16_t, bf16_t) }
 #undef OUTLETS_NORMS_V
+#undef OUTLETS_NORMS_L
 }
 
 void launch_rmsnorm(int act_fmt, int gamma_fmt, int rows, int d, const float* x, int64_t ldx,

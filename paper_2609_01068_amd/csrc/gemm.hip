@@ -1,21 +1,20 @@
 // Dense contractions of the draft layer and the length head on gfx950.
 //
-// bf16 / e4m3-weight path: 256x256x64 workgroup tiles, 8 waves (4 x 2), each
-// wave owning a 64x128 sub-tile built from v_mfma_f32_16x16x32_bf16 blocks
-// (measured 2-6% faster than the same tiling on 32x32x16 blocks); two waves
-// per SIMD let one issue MFMAs while the other waits on LDS (measured faster
-// than 4 waves of 128x128 at one wave per SIMD).  K
-// slices move global -> LDS by DMA (global_load_lds_dwordx4), so no registers
-// stage them; two LDS stages let the copy of slice k+1 run under the MFMAs of
-// slice k, with one wait + barrier per slice.  16-byte LDS chunks are
-// XOR-swizzled per row (the swizzle is applied to the DMA source addresses,
-// since each lane's LDS slot is fixed), making fragment reads conflict free.
-// e4m3 weights stay as codes in LDS, are widened to bf16 (exact) when a
-// fragment is read, and the per-row scale is applied in the epilogue.
+// bf16 / e4m3-weight path: v_mfma_f32_16x16x32_bf16 blocks (measured 2-6%
+// faster than the same tiling on 32x32x16 blocks) on 256 x 256 x 64 tiles
+// for large calls (gemm_mfma_256x256) and on 64 or 128 x 256 tiles for calls
+// with few rows (gemm_mfma_short).  K slices move global -> LDS by DMA
+// (buffer_load_dwordx4 ... lds), so no registers stage them.  16-byte LDS
+// chunks are XOR-swizzled per row (the swizzle is applied to the DMA source
+// addresses, since each lane's LDS slot is fixed), making fragment reads
+// conflict free.  e4m3 weights stay as codes in LDS, are widened to bf16
+// (exact) when they are multiplied, and the per-row scale is applied in the
+// epilogue.
 //
 // fp32 path (the fp32 layer): v_mfma_f32_16x16x4_f32 tiles with full bounds
 // handling, see below.
 #include <algorithm>
+#include <type_traits>
 
 #include "common.hpp"
 #include "kernels.hpp"
@@ -25,32 +24,17 @@ namespace outlets {
 
 namespace {
 
-// Tile shape of the MFMA GEMM (measured choices; override at build time to tune).
-#ifndef OUTLETS_GEMM_WM
-#define OUTLETS_GEMM_WM 4
-#endif
-#ifndef OUTLETS_GEMM_WN
-#define OUTLETS_GEMM_WN 2
-#endif
-#ifndef OUTLETS_GEMM_BK
-#define OUTLETS_GEMM_BK 64
-#endif
-#ifndef OUTLETS_GEMM_STAGES
-#define OUTLETS_GEMM_STAGES 2
-#endif
-#ifndef OUTLETS_GEMM_IGLP
-#define OUTLETS_GEMM_IGLP 0
-#endif
 #ifndef OUTLETS_GEMM_SPLITMAP
 #define OUTLETS_GEMM_SPLITMAP 2   // K-split launches dealt split-major over the XCDs (0 = by tile; 1 = small-M splits only)
 #endif
 #ifndef OUTLETS_GEMM_GMFULL
 #define OUTLETS_GEMM_GMFULL 4     // up to this many row tiles, one group holds them all (0 = off)
 #endif
-#ifndef OUTLETS_GEMM_DMAW
-#define OUTLETS_GEMM_DMAW 4   // waves that issue the LDS copies (0 = all)
-#endif
-constexpr int BK = OUTLETS_GEMM_BK;
+constexpr int BK = 64;                // K slice
+// LDS is read through vector types: for the runtime's struct types (uint2) the
+// compiler cannot tell the read from a copy in flight and waits for all of them.
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ int swz(int row, int c) { return row * 8 + (c ^ ((row >> 1) & 7)); }
 
@@ -146,36 +130,134 @@ __device__ __forceinline__ int swz_chunk(int row, int c) {
     return c ^ ((row / (256 / ROWB)) % (ROWB / 16));
 }
 
+// Writes one wave's FM x FN accumulator blocks (rows m0 + row0 .., columns n0
+// + col0 .. of the tile at m0, n0) with the epilogue EPI.
+template <int EPI, bool E4M3, int BM, int FM, int FN>
+__device__ __forceinline__ void gemm_epilogue(f32x4 (&acc)[FM][FN], int M, const GemmB& B, const GemmC& C, int m0,
+                                              int n0, int row0, int col0, int split, int64_t slot) {
+    constexpr int BN = 256;
+    const int lane = threadIdx.x & 63, grp = lane >> 4, l16 = lane & 15;
+    // epilogue: lane holds column l16 of each 16x16 block, rows 4 g + q for
+    // accumulator element q.  Outputs (and the residual) go through
+    // descriptors based at the tile's first row whose size ends at row M:
+    // stores to rows past M are dropped by the range check, so there are no
+    // per-element branches, and the offsets are 32-bit.  EPI_PARTIAL_TILE
+    // writes the whole tile to its own 256 x 256 block `slot` of the workspace.
+    constexpr bool F32OUT = EPI == EPI_STORE_F32 || EPI == EPI_RESID_F32 || EPI == EPI_PARTIAL ||
+                            EPI == EPI_PARTIAL_TILE;
+    constexpr int OSZ = F32OUT ? 4 : 2;   // activations are bf16
+    const int rows_valid = EPI == EPI_PARTIAL_TILE ? BM : min(BM, M - m0);
+    const int ldc = EPI == EPI_PARTIAL_TILE ? BN : static_cast<int>(C.ldc);   // tile offsets fit 32 bits
+    const int ncol0 = EPI == EPI_PARTIAL_TILE ? n0 : 0;       // column origin of the output block
+    char* cbase =
+        EPI == EPI_PARTIAL_TILE
+            ? static_cast<char*>(C.c) + slot * (BM * BN * 4)
+            : static_cast<char*>(C.c) +
+                  ((EPI == EPI_PARTIAL ? (int64_t)split * C.split_stride : 0) + (int64_t)m0 * C.ldc) * OSZ;
+    const __amdgpu_buffer_rsrc_t rc = buf_rsrc(cbase, (int64_t)rows_valid * ldc * OSZ);
+    const int ldr = static_cast<int>(C.ldr);
+    const __amdgpu_buffer_rsrc_t rr =
+        EPI == EPI_RESID_F32 ? buf_rsrc(C.resid + (int64_t)m0 * C.ldr, (int64_t)rows_valid * C.ldr * 4) : rc;
+    auto put = [&](uint32_t off, float v) {
+        if constexpr (OSZ == 4) {
+            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), rc, off, 0, 0);
+        } else {
+            __builtin_amdgcn_raw_buffer_store_b16(f32_to_bf16(v), rc, off, 0, 0);
+        }
+    };
+    // The residual may alias the output (in-place update): the residuals of
+    // JB column blocks are loaded before any of their stores, so the loads
+    // overlap instead of each block waiting out a full memory latency.
+    constexpr int JB = (EPI == EPI_RESID_F32) ? 4 : 1;
+    static_assert(FN % JB == 0, "column blocks per residual batch");
+#pragma unroll
+    for (int j0 = 0; j0 < FN; j0 += JB) {
+        float rv[JB][EPI == EPI_RESID_F32 ? FM : 1][4];
+        if (EPI == EPI_RESID_F32) {
+            // one lane offset; the row step goes in the scalar offset
+            const uint32_t vb = static_cast<uint32_t>(((row0 + 4 * grp) * ldr + n0 + col0 + l16) * 4);
+#pragma unroll
+            for (int jj = 0; jj < JB; ++jj)
+#pragma unroll
+                for (int i = 0; i < FM; ++i)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        rv[jj][i][q] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
+                            rr, vb + (j0 + jj) * 64, (i * 16 + q) * ldr * 4, 0));
+        }
+#pragma unroll
+        for (int jj = 0; jj < JB; ++jj) {
+            const int j = j0 + jj;
+            const int n = n0 + col0 + j * 16 + l16;
+            // SwiGLU: 32-column gate/up blocks, so 16-wide blocks j, j + 1 are
+            // gate and j + 2, j + 3 the matching up columns
+            const bool gate_blk = EPI == EPI_SWIGLU && (j & 3) < 2;
+            float sc = 1.f, sc_u = 1.f;
+            if (E4M3) {
+                int sg, r;
+                b_row(B, n, sg, r);
+                sc = bf16_to_f32(B.scale[sg][r]);
+                if (gate_blk) {
+                    b_row(B, n + 32, sg, r);
+                    sc_u = bf16_to_f32(B.scale[sg][r]);
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < FM; ++i) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int row = row0 + i * 16 + 4 * grp + q;
+                    const float v = acc[i][j][q] * sc;
+                    if (EPI == EPI_STORE_F32 || EPI == EPI_STORE_ACT || EPI == EPI_PARTIAL ||
+                        EPI == EPI_PARTIAL_TILE) {
+                        put(static_cast<uint32_t>((row * ldc + n - ncol0) * OSZ), v);
+                    } else if (EPI == EPI_RESID_F32) {
+                        put(static_cast<uint32_t>((row * ldc + n) * OSZ), rv[jj][i][q] + v);
+                    } else if (EPI == EPI_SWIGLU) {
+                        if (gate_blk) {
+                            const float g = v, u = acc[i][j + 2][q] * sc_u;
+                            const int f = ((n >> 5) >> 1) * 32 + (n & 31);
+                            put(static_cast<uint32_t>((row * ldc + f) * OSZ), silu_f(g) * u);
+                        }
+                    }
+                }
+            }
+            // keep the compiler from hoisting the next block's conversions
+            // over this one (it would run out of registers)
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+}
+
 // K-slice layout inside one BK step: 32-deep MFMA step st gives lane group
 // g = lane / 16 the 8 k-values 32 st + 8 g + (0..7), i.e. 16-byte chunk
 // 4 st + g of a bf16 row (bytes 32 st + 8 g .. +7 of an e4m3 row).  A and B
 // use the same assignment, so every product pairs equal k.
 //
-// Tiles are BM = 64 WM rows by 256 columns on WM x WN waves: 256 x 256 on
-// 4 x 2 waves for large M, 128 x 256 on 2 x 4 and 64 x 256 on 1 x 4 for
-// calls with few rows (the kernel keeps its 256 x 256 name).
+// Tiles are BM = 64 WM rows by 256 columns on WM x 4 waves of 64 x 64:
+// 64 x 256 and 128 x 256.
 //
 // LDS per stage: A [BM rows][BK bf16], then B [256 rows][BK bf16] or, for
 // e4m3, [256 rows][BK codes].  STAGES slices are in flight: slice k + STAGES
 // - 1 is copied while slice k is multiplied.
-template <int EPI, bool E4M3, bool PF, int WM, int WN, int BK, int STAGES>
-__global__ void __launch_bounds__(WM * WN * 64)
-gemm_mfma_256x256(int M, int N, int K, GemmA A, GemmB B, GemmC C, int k_per_split, int pid0) {
-    constexpr int BM = 64 * WM, BN = 256, NW = WM * WN;   // 64-row wave tiles (FM = 4)
+template <int EPI, bool E4M3, int WM, int STAGES>
+__global__ void __launch_bounds__(WM * 256)
+gemm_mfma_short(int M, int N, int K, GemmA A, GemmB B, GemmC C, int k_per_split, int pid0) {
+    constexpr int WN = 4, BM = 64 * WM, BN = 256, NW = WM * WN;
     constexpr int TM = BM / WM, TN = BN / WN, FM = TM / 16, FN = TN / 16;
     constexpr int KSTEPS = BK / 32;
     constexpr int AROWB = BK * 2;                       // bytes per A row
     constexpr int BROWB = E4M3 ? BK : BK * 2;           // bytes per B row
     constexpr int A_BYTES = BM * AROWB, B_BYTES = BN * BROWB;
     constexpr int STAGE = A_BYTES + B_BYTES;
-    constexpr int DW = (OUTLETS_GEMM_DMAW > 0 && OUTLETS_GEMM_DMAW < NW) ? OUTLETS_GEMM_DMAW : NW;
+    constexpr int DW = 4;                               // waves that issue the copies, one per SIMD
     constexpr int ACP = A_BYTES / 1024 / DW;            // DMA copies per issuing wave and slice
     constexpr int BCP = B_BYTES / 1024 / DW;
     constexpr int ARPC = 64 / (AROWB / 16);             // rows per DMA copy
     constexpr int BRPC = 64 / (BROWB / 16);
     static_assert(ACP >= 1 && BCP >= 1, "tile too small for the wave count");
     static_assert(BK % 32 == 0, "K slices are whole 32-deep MFMA steps");
-    __shared__ __attribute__((aligned(16))) char lds[STAGES * STAGE + (PF ? 1024 : 0)];
+    __shared__ __attribute__((aligned(16))) char lds[STAGES * STAGE];
 
     // this launch covers tiles pid0 .. pid0 + gridDim.x - 1 of the tile order
     // in gridDim.y K splits.  Workgroups reach the XCDs round-robin in
@@ -241,19 +323,11 @@ gemm_mfma_256x256(int M, int N, int K, GemmA A, GemmB B, GemmC C, int k_per_spli
         b_row(B, n0 + row, sgm, r);
         b_voff[j] = static_cast<uint32_t>((int64_t)(r - r0) * B.ld * ESZ + c * 16);
     }
-    // PF: L2 prefetch of the A rows of the slice after the one being copied
-    // (one 16-byte LDS copy per 128-byte row segment, one row per lane of the
-    // issuing waves, landing in a 1 KiB area nobody reads).  It shortens the
-    // wait for activation rows streamed from HBM on narrow outputs; the same
-    // prefetch of B rows measured slower on every shape.
-    constexpr int PFOPS = PF ? 1 : 0;
     // 64-row tiles (calls of at most 64 rows) read every weight byte once:
     // non-temporal weight copies (measured: the draft model head's 1 GB
     // weight stream 10% faster, the other small-M GEMMs unchanged)
     constexpr int BNT = WM == 1 ? 2 : 0;
-    static_assert(!PF || DW * 64 == BM, "prefetch assumes 64 rows per issuing wave");
-    const uint32_t a_pf = PF ? static_cast<uint32_t>(min(dwave * 64 + lane, a_rows - 1) * A.ld * 2) : 0u;
-    auto issue = [&](int k0, int stage, int kpf) {
+    auto issue = [&](int k0, int stage) {
         if (DW < NW && !issuer) return;
         char* base = lds + stage * STAGE;
         // the slice's K offset is uniform: it goes in the scalar offset
@@ -265,11 +339,6 @@ gemm_mfma_256x256(int M, int N, int K, GemmA A, GemmB B, GemmC C, int k_per_spli
 #pragma unroll
         for (int j = 0; j < BCP; ++j)
             dma16<BNT>(rb[j], b_voff[j], base + A_BYTES + (dwave * BCP + j) * 1024, static_cast<uint32_t>(k0 * ESZ));
-        if constexpr (PF) {
-            const int sp = kpf / A.kseg;
-            const __amdgpu_buffer_rsrc_t rsp = sp == 0 ? ra[0] : (sp == 1 ? ra[1] : ra[2]);
-            dma16(rsp, a_pf + static_cast<uint32_t>((kpf - sp * A.kseg) * 2), lds + STAGES * STAGE);
-        }
     };
 
     const int grp = lane >> 4, l16 = lane & 15;
@@ -298,7 +367,7 @@ gemm_mfma_256x256(int M, int N, int K, GemmA A, GemmB B, GemmC C, int k_per_spli
             if (E4M3) {
                 // 8 codes = one half of 16-byte chunk 2 st + g / 2
                 const int c = 2 * st + (grp >> 1);
-                const uint2 codes = *reinterpret_cast<const uint2*>(
+                const u32x2 codes = *reinterpret_cast<const u32x2*>(
                     bb + row * BROWB + (swz_chunk<BROWB>(row, c) << 4) + 8 * (grp & 1));
                 uint32_t w0, w1, w2, w3;
                 e4m3x4_to_bf16x4(codes.x, w0, w1);
@@ -320,12 +389,11 @@ gemm_mfma_256x256(int M, int N, int K, GemmA A, GemmB B, GemmC C, int k_per_spli
     if (nk_loop > 0) {
 #pragma unroll
         for (int p = 0; p < STAGES - 1; ++p)
-            issue(kb + min(p, nk_loop - 1) * BK, p, kb + min(p + 1, nk_loop - 1) * BK);
+            issue(kb + min(p, nk_loop - 1) * BK, p);
     }
     for (int it = 0; it < nk_loop; ++it) {
-        // this wave's copies of slice `it` landed (later slices' ops and the
-        // prefetch issued after them may be pending)
-        wait_dma<(STAGES - 2) * (OPS + PFOPS) + PFOPS>();
+        // this wave's copies of slice `it` landed (later slices' may be pending)
+        wait_dma<(STAGES - 2) * OPS>();
         barrier_no_fence();   // every wave's copies of slice `it` are in LDS; slice it-1 is consumed
         // past the end, re-copy the last slice into a stage nobody reads again:
         // the loop body stays one basic block, which the scheduler needs.
@@ -333,8 +401,7 @@ gemm_mfma_256x256(int M, int N, int K, GemmA A, GemmB B, GemmC C, int k_per_spli
         // the first 32-deep step's MFMAs (measured: the other order is 10%
         // slower for bf16 and 3-5% slower for e4m3)
         const int k_next = kb + min(it + STAGES - 1, nk_loop - 1) * BK;
-        const int k_pf = kb + min(it + STAGES, nk_loop - 1) * BK;
-        if (!E4M3) issue(k_next, (it + STAGES - 1) % STAGES, k_pf);
+        if (!E4M3) issue(k_next, (it + STAGES - 1) % STAGES);
         const char* base = lds + (it % STAGES) * STAGE;
         bf16x8 af[2][FM], bfr[2][FN];
         load_a(base, 0, af[0]);
@@ -350,72 +417,62 @@ gemm_mfma_256x256(int M, int N, int K, GemmA A, GemmB B, GemmC C, int k_per_spli
 #pragma unroll
                 for (int j = 0; j < FN; ++j)
                     acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[st & 1][i], bfr[st & 1][j], acc[i][j], 0, 0, 0);
-            if (E4M3 && st == 0) issue(k_next, (it + STAGES - 1) % STAGES, k_pf);
+            if (E4M3 && st == 0) issue(k_next, (it + STAGES - 1) % STAGES);
         }
-#if OUTLETS_GEMM_IGLP >= 0
-        __builtin_amdgcn_iglp_opt(OUTLETS_GEMM_IGLP);   // interleave LDS reads with MFMAs
-#endif
+        __builtin_amdgcn_iglp_opt(0);   // interleave LDS reads with MFMAs
     }
     wait_dma<0>();   // no LDS copy may outlive the workgroup
 
-    // epilogue: lane holds column l16 of each 16x16 block, rows 4 g + q for
-    // accumulator element q.  Outputs (and the residual) go through
-    // descriptors based at the tile's first row whose size ends at row M:
-    // stores to rows past M are dropped by the range check, so there are no
-    // per-element branches, and the offsets are 32-bit.  EPI_PARTIAL_TILE
-    // writes the whole tile to its own 256 x 256 block of the workspace,
-    // (split, tile of this launch) in that order.
-    constexpr bool F32OUT = EPI == EPI_STORE_F32 || EPI == EPI_RESID_F32 || EPI == EPI_PARTIAL ||
-                            EPI == EPI_PARTIAL_TILE;
-    constexpr int OSZ = F32OUT ? 4 : 2;   // activations are bf16
-    const int rows_valid = EPI == EPI_PARTIAL_TILE ? BM : min(BM, M - m0);
-    const int ldc = EPI == EPI_PARTIAL_TILE ? BN : static_cast<int>(C.ldc);   // tile offsets fit 32 bits
-    const int ncol0 = EPI == EPI_PARTIAL_TILE ? n0 : 0;       // column origin of the output block
-    char* cbase =
-        EPI == EPI_PARTIAL_TILE
-            ? static_cast<char*>(C.c) + ((int64_t)split * gridDim.x + (tpid - pid0)) * (BM * BN * 4)
-            : static_cast<char*>(C.c) +
-                  ((EPI == EPI_PARTIAL ? (int64_t)split * C.split_stride : 0) + (int64_t)m0 * C.ldc) * OSZ;
-    const __amdgpu_buffer_rsrc_t rc = buf_rsrc(cbase, (int64_t)rows_valid * ldc * OSZ);
-    const int ldr = static_cast<int>(C.ldr);
-    const __amdgpu_buffer_rsrc_t rr =
-        EPI == EPI_RESID_F32 ? buf_rsrc(C.resid + (int64_t)m0 * C.ldr, (int64_t)rows_valid * C.ldr * 4) : rc;
-    auto put = [&](uint32_t off, float v) {
-        if constexpr (OSZ == 4) {
-            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), rc, off, 0, 0);
-        } else {
-            __builtin_amdgcn_raw_buffer_store_b16(f32_to_bf16(v), rc, off, 0, 0);
+    gemm_epilogue<EPI, E4M3, BM, FM, FN>(acc, M, B, C, m0, n0, wm * TM, wn * TN, split,
+                                         (int64_t)split * gridDim.x + (tpid - pid0));
+}
+
+// Writes the 8 x 4 accumulator blocks of one wave of gemm_mfma_256x256 (rows row0 ..
+// row0 + 127 and columns col0 .. col0 + 63 of the tile at m0, n0).  Column
+// l16 of blocks 2 h and 2 h + 1 is columns 32 h + 2 l16 and + 1, so a lane
+// holds neighbouring columns: bf16 pairs leave as one 4-byte store (64
+// contiguous bytes per row) and fp32 pairs as one 8-byte store (128 bytes,
+// a whole line).  EPI_PARTIAL_TILE writes the tile to its own 256 x 256 block
+// `slot` of the workspace.
+template <int EPI, bool E4M3>
+__device__ __forceinline__ void gemm_epilogue_pairs(f32x4 (&acc)[8][4], int M, const GemmB& B, const GemmC& C, int m0,
+                                                    int n0, int row0, int col0, int split, int64_t slot) {
+    constexpr int BM = 256, BN = 256, FM = 8;
+    const int lane = threadIdx.x & 63, grp = lane >> 4, l16 = lane & 15;
+    auto pack = [](float lo, float hi) { return f32_to_bf16(lo) | (uint32_t(f32_to_bf16(hi)) << 16); };
+    // e4m3: the row scales of the lane's four columns (columns of half h at
+    // hcol[h], + 1)
+    auto scales = [&](int n, float& s0, float& s1) {
+        s0 = s1 = 1.f;
+        if (E4M3) {
+            int sg, r;
+            b_row(B, n, sg, r);
+            s0 = bf16_to_f32(B.scale[sg][r]);
+            s1 = bf16_to_f32(B.scale[sg][r + 1]);
         }
     };
     if constexpr (EPI == EPI_QKV_ROPE) {
-        // A wave's 128 columns are one head (head dim 128): q, k, v or gate.
-        // Rotate-half pairs (c, c + 64) are blocks j and j + 4 of the same
-        // lane, so the rotation is applied to the fp32 accumulators.  q and
-        // gate go to C; k (rotated) and v go straight into the KV pages
-        // (K [page][kv head][16 tokens][128], V [page][kv head][128][16]).
-        static_assert(TN == 128 && FN == 8, "one 128-wide head per wave");
+        // A wave's columns are channels c0 .. c0 + 31 and c0 + 64 .. c0 + 95
+        // of one 128-wide head (q, k, v or gate): rotate-half pairs (c, c +
+        // 64) sit in the same lane, so the rotation is applied to the fp32
+        // accumulators.  q and gate go to C; k (rotated) and v go straight
+        // into the KV pages (K [page][kv head][16 tokens][128], V
+        // [page][kv head][128][16]).
         const RopeKV& R = C.rope;
-        const int hcol0 = n0 + wn * TN, head = hcol0 / 128;
+        const int head = (n0 + col0) / 128, hcol0 = head * 128;
+        const int c = (col0 & 64) / 2 + 2 * l16;           // this lane: channels c, c + 1, c + 64, c + 65
         const int region = head < R.n_q ? 0 : (head < R.n_q + R.n_kv ? 1 : (head < R.n_q + 2 * R.n_kv ? 2 : 3));
         const int kvh = region == 1 ? head - R.n_q : head - R.n_q - R.n_kv;
-        float sc[FN];
-#pragma unroll
-        for (int j = 0; j < FN; ++j) {
-            sc[j] = 1.f;
-            if (E4M3) {
-                int sg, r;
-                b_row(B, hcol0 + j * 16 + l16, sg, r);
-                sc[j] = bf16_to_f32(B.scale[sg][r]);
-            }
-        }
-        bf16_t* cq = static_cast<bf16_t*>(C.c);
+        float sc[4];
+        scales(hcol0 + c, sc[0], sc[1]);
+        scales(hcol0 + c + 64, sc[2], sc[3]);
         if (region == 2) {
             // V pages hold each channel's 16 tokens contiguously: a lane's 4
             // consecutive rows go out as one 8-byte (or two 4-byte) store per
             // channel when they are consecutive positions on one page
 #pragma unroll
             for (int i = 0; i < FM; ++i) {
-                const int t0 = m0 + wm * TM + i * 16 + 4 * grp;
+                const int t0 = m0 + row0 + i * 16 + 4 * grp;
                 int pos[4], page[4];
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
@@ -427,24 +484,16 @@ gemm_mfma_256x256(int M, int N, int K, GemmA A, GemmB B, GemmC C, int k_per_spli
                                   page[1] == page[0] && page[2] == page[0] && pos[1] == pos[0] + 1 &&
                                   pos[2] == pos[0] + 2;
                 const int off0 = pos[0] & 15;
-                if (run4 && (off0 & 3) == 0) {
+                if (run4 && (off0 & 1) == 0) {
                     bf16_t* vb = R.vpool + ((int64_t)page[0] * R.n_kv + kvh) * 128 * 16 + off0;
 #pragma unroll
-                    for (int j = 0; j < FN; ++j) {
+                    for (int j = 0; j < 4; ++j) {
                         const float s = sc[j];
-                        uint2 pk;
-                        pk.x = f32_to_bf16(acc[i][j][0] * s) | (uint32_t(f32_to_bf16(acc[i][j][1] * s)) << 16);
-                        pk.y = f32_to_bf16(acc[i][j][2] * s) | (uint32_t(f32_to_bf16(acc[i][j][3] * s)) << 16);
-                        *reinterpret_cast<uint2*>(vb + (j * 16 + l16) * 16) = pk;
-                    }
-                } else if (run4 && (off0 & 1) == 0) {
-                    bf16_t* vb = R.vpool + ((int64_t)page[0] * R.n_kv + kvh) * 128 * 16 + off0;
-#pragma unroll
-                    for (int j = 0; j < FN; ++j) {
-                        const float s = sc[j];
-                        uint32_t* d = reinterpret_cast<uint32_t*>(vb + (j * 16 + l16) * 16);
-                        d[0] = f32_to_bf16(acc[i][j][0] * s) | (uint32_t(f32_to_bf16(acc[i][j][1] * s)) << 16);
-                        d[1] = f32_to_bf16(acc[i][j][2] * s) | (uint32_t(f32_to_bf16(acc[i][j][3] * s)) << 16);
+                        uint32_t* d = reinterpret_cast<uint32_t*>(vb + (c + (j & 1) + 64 * (j >> 1)) * 16);
+                        const uint32_t lo = pack(acc[i][j][0] * s, acc[i][j][1] * s);
+                        const uint32_t hi = pack(acc[i][j][2] * s, acc[i][j][3] * s);
+                        if ((off0 & 3) == 0) *reinterpret_cast<uint2*>(d) = make_uint2(lo, hi);
+                        else { d[0] = lo; d[1] = hi; }
                     }
                 } else {
 #pragma unroll
@@ -452,7 +501,8 @@ gemm_mfma_256x256(int M, int N, int K, GemmA A, GemmB B, GemmC C, int k_per_spli
                         if (t0 + q >= M) continue;
                         bf16_t* vb = R.vpool + ((int64_t)page[q] * R.n_kv + kvh) * 128 * 16 + (pos[q] & 15);
 #pragma unroll
-                        for (int j = 0; j < FN; ++j) vb[(j * 16 + l16) * 16] = f32_to_bf16(acc[i][j][q] * sc[j]);
+                        for (int j = 0; j < 4; ++j)
+                            vb[(c + (j & 1) + 64 * (j >> 1)) * 16] = f32_to_bf16(acc[i][j][q] * sc[j]);
                     }
                 }
             }
@@ -462,96 +512,317 @@ gemm_mfma_256x256(int M, int N, int K, GemmA A, GemmB B, GemmC C, int k_per_spli
         for (int i = 0; i < FM; ++i) {
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const int t = m0 + wm * TM + i * 16 + 4 * grp + q;
+                const int t = m0 + row0 + i * 16 + 4 * grp + q;
                 if (t >= M) continue;
-                bf16_t* crow = cq + (int64_t)t * C.ldc + hcol0;
-                if (region == 3) {
-#pragma unroll
-                    for (int j = 0; j < FN; ++j) crow[j * 16 + l16] = f32_to_bf16(acc[i][j][q] * sc[j]);
-                    continue;
+                const float x[4] = {acc[i][0][q] * sc[0], acc[i][1][q] * sc[1], acc[i][2][q] * sc[2], acc[i][3][q] * sc[3]};
+                bf16_t* dst = static_cast<bf16_t*>(C.c) + (int64_t)t * C.ldc + hcol0;
+                float2 cs = {1.f, 1.f}, sn = {0.f, 0.f};
+                if (region < 2) {
+                    const int pos = R.tok_pos[t];
+                    cs = *reinterpret_cast<const float2*>(R.cos_t + (int64_t)pos * 64 + c);
+                    sn = *reinterpret_cast<const float2*>(R.sin_t + (int64_t)pos * 64 + c);
+                    if (region == 1) {
+                        const int page = R.page_table[(int64_t)R.tok_slot[t] * R.max_pages + (pos >> 4)];
+                        dst = R.kpool + (((int64_t)page * R.n_kv + kvh) * 16 + (pos & 15)) * 128;
+                    }
                 }
-                const int pos = R.tok_pos[t];
-                const float* cr = R.cos_t + (int64_t)pos * 64;
-                const float* sr = R.sin_t + (int64_t)pos * 64;
-                bf16_t* dst = crow;
-                if (region == 1) {
-                    const int page = R.page_table[(int64_t)R.tok_slot[t] * R.max_pages + (pos >> 4)];
-                    dst = R.kpool + (((int64_t)page * R.n_kv + kvh) * 16 + (pos & 15)) * 128;
-                }
-#pragma unroll
-                for (int j = 0; j < FN / 2; ++j) {
-                    const int c = j * 16 + l16;
-                    const float x1 = acc[i][j][q] * sc[j], x2 = acc[i][j + 4][q] * sc[j + 4];
-                    const float cs = cr[c], sn = sr[c];
-                    dst[c] = f32_to_bf16(x1 * cs - x2 * sn);
-                    dst[c + 64] = f32_to_bf16(x2 * cs + x1 * sn);
-                }
+                const bool rot = region < 2;
+                *reinterpret_cast<uint32_t*>(dst + c) =
+                    rot ? pack(x[0] * cs.x - x[2] * sn.x, x[1] * cs.y - x[3] * sn.y) : pack(x[0], x[1]);
+                *reinterpret_cast<uint32_t*>(dst + c + 64) =
+                    rot ? pack(x[2] * cs.x + x[0] * sn.x, x[3] * cs.y + x[1] * sn.y) : pack(x[2], x[3]);
             }
         }
         return;
     }
-    // The residual may alias the output (in-place update): the residuals of
-    // JB column blocks are loaded before any of their stores, so the loads
-    // overlap instead of each block waiting out a full memory latency.
-    constexpr int JB = (EPI == EPI_RESID_F32) ? 4 : 1;
-    static_assert(FN % JB == 0, "column blocks per residual batch");
+    // Outputs (and the residual) go through descriptors based at the tile's
+    // first row whose size ends at row M: stores to rows past M are dropped
+    // by the range check, and the offsets are 32-bit.
+    constexpr bool F32OUT = EPI == EPI_STORE_F32 || EPI == EPI_RESID_F32 || EPI == EPI_PARTIAL || EPI == EPI_PARTIAL_TILE;
+    constexpr int OSZ = F32OUT ? 4 : 2;   // activations are bf16
+    const int rows_valid = EPI == EPI_PARTIAL_TILE ? BM : min(BM, M - m0);
+    const int ldc = EPI == EPI_PARTIAL_TILE ? BN : static_cast<int>(C.ldc);
+    char* cbase = EPI == EPI_PARTIAL_TILE
+                      ? static_cast<char*>(C.c) + slot * (BM * BN * 4)
+                      : static_cast<char*>(C.c) +
+                            ((EPI == EPI_PARTIAL ? (int64_t)split * C.split_stride : 0) + (int64_t)m0 * C.ldc) * OSZ;
+    const __amdgpu_buffer_rsrc_t rc = buf_rsrc(cbase, (int64_t)rows_valid * ldc * OSZ);
+    const int ldr = static_cast<int>(C.ldr);
+    const __amdgpu_buffer_rsrc_t rr =
+        EPI == EPI_RESID_F32 ? buf_rsrc(C.resid + (int64_t)m0 * C.ldr, (int64_t)rows_valid * C.ldr * 4) : rc;
+    const int rl = row0 + 4 * grp;                          // + 16 i + q
 #pragma unroll
-    for (int j0 = 0; j0 < FN; j0 += JB) {
-        float rv[JB][EPI == EPI_RESID_F32 ? FM : 1][4];
-        if (EPI == EPI_RESID_F32) {
-            // one lane offset; the row step goes in the scalar offset
-            const uint32_t vb = static_cast<uint32_t>(((wm * TM + 4 * grp) * ldr + n0 + wn * TN + l16) * 4);
+    for (int h = 0; h < (EPI == EPI_SWIGLU ? 1 : 2); ++h) {
+        const int n = n0 + col0 + 32 * h + 2 * l16;
+        // SwiGLU: 32-column gate/up blocks, so blocks 0, 1 are gate and 2, 3 up
+        const int no = EPI == EPI_SWIGLU ? (n0 + col0) / 2 + 2 * l16 : (EPI == EPI_PARTIAL_TILE ? n - n0 : n);
+        float s0, s1, u0 = 1.f, u1 = 1.f;
+        scales(n, s0, s1);
+        if (EPI == EPI_SWIGLU) scales(n + 32, u0, u1);
+        // The residual may alias the output (in-place update): a half's
+        // residuals are loaded four row blocks at a time before any of their
+        // stores, so the loads overlap.
+        constexpr int IB = 4;
 #pragma unroll
-            for (int jj = 0; jj < JB; ++jj)
+        for (int i0 = 0; i0 < FM; i0 += IB) {
+            float2 rv[EPI == EPI_RESID_F32 ? IB : 1][4];
+            if (EPI == EPI_RESID_F32) {
 #pragma unroll
-                for (int i = 0; i < FM; ++i)
+                for (int i = 0; i < IB; ++i)
 #pragma unroll
-                    for (int q = 0; q < 4; ++q)
-                        rv[jj][i][q] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
-                            rr, vb + (j0 + jj) * 64, (i * 16 + q) * ldr * 4, 0));
-        }
-#pragma unroll
-        for (int jj = 0; jj < JB; ++jj) {
-            const int j = j0 + jj;
-            const int n = n0 + wn * TN + j * 16 + l16;
-            // SwiGLU: 32-column gate/up blocks, so 16-wide blocks j, j + 1 are
-            // gate and j + 2, j + 3 the matching up columns
-            const bool gate_blk = EPI == EPI_SWIGLU && (j & 3) < 2;
-            float sc = 1.f, sc_u = 1.f;
-            if (E4M3) {
-                int sg, r;
-                b_row(B, n, sg, r);
-                sc = bf16_to_f32(B.scale[sg][r]);
-                if (gate_blk) {
-                    b_row(B, n + 32, sg, r);
-                    sc_u = bf16_to_f32(B.scale[sg][r]);
-                }
+                    for (int q = 0; q < 4; ++q) {
+                        const auto v = __builtin_amdgcn_raw_buffer_load_b64(rr, static_cast<uint32_t>((rl * ldr + n) * 4),
+                                                                            ((i0 + i) * 16 + q) * ldr * 4, 0);
+                        rv[i][q] = make_float2(__uint_as_float(v[0]), __uint_as_float(v[1]));
+                    }
             }
 #pragma unroll
-            for (int i = 0; i < FM; ++i) {
+            for (int i = 0; i < IB; ++i)
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    const int row = wm * TM + i * 16 + 4 * grp + q;
-                    const float v = acc[i][j][q] * sc;
-                    if (EPI == EPI_STORE_F32 || EPI == EPI_STORE_ACT || EPI == EPI_PARTIAL ||
-                        EPI == EPI_PARTIAL_TILE) {
-                        put(static_cast<uint32_t>((row * ldc + n - ncol0) * OSZ), v);
-                    } else if (EPI == EPI_RESID_F32) {
-                        put(static_cast<uint32_t>((row * ldc + n) * OSZ), rv[jj][i][q] + v);
-                    } else if (EPI == EPI_SWIGLU) {
-                        if (gate_blk) {
-                            const float g = v, u = acc[i][j + 2][q] * sc_u;
-                            const int f = ((n >> 5) >> 1) * 32 + (n & 31);
-                            put(static_cast<uint32_t>((row * ldc + f) * OSZ), silu_f(g) * u);
-                        }
+                    const int ii = i0 + i;
+                    const uint32_t off = static_cast<uint32_t>(((rl + 16 * ii + q) * ldc + no) * OSZ);
+                    float v0 = acc[ii][2 * h][q] * s0, v1 = acc[ii][2 * h + 1][q] * s1;
+                    if (EPI == EPI_SWIGLU) {
+                        v0 = silu_f(v0) * (acc[ii][2][q] * u0);
+                        v1 = silu_f(v1) * (acc[ii][3][q] * u1);
+                    }
+                    if (EPI == EPI_RESID_F32) { v0 = rv[i][q].x + v0; v1 = rv[i][q].y + v1; }
+                    if constexpr (OSZ == 4) {
+                        __builtin_amdgcn_raw_buffer_store_b64(u32x2{__float_as_uint(v0), __float_as_uint(v1)}, rc, off, 0, 0);
+                    } else {
+                        __builtin_amdgcn_raw_buffer_store_b32(pack(v0, v1), rc, off, 0, 0);
                     }
                 }
-            }
-            // keep the compiler from hoisting the next block's conversions
-            // over this one (it would run out of registers)
-            __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_sched_barrier(0);   // one batch of conversions at a time (registers)
         }
     }
+}
+
+// Large calls: 256 x 256 tiles on 8 waves in two groups of four (waves 0-3: the
+// tile's first 128 rows, waves 4-7: the last; wave w and w + 4 share a SIMD),
+// each wave 128 x 64 of 16x16x32 blocks.  A 64-deep K slice takes four phases,
+// one 64 x 32 quadrant of the wave's outputs (16 MFMAs) each; a phase first
+// reads the fragments it lacks from LDS and issues one half-slice copy, then
+// multiplies.  The groups run half a phase apart (group 1 enters one barrier
+// late), so on every SIMD one wave multiplies while the other reads, and the
+// matrix pipe waits neither for LDS nor for a slice barrier.  Measured
+// against a 4 x 2-wave kernel with one barrier per slice and two LDS stages
+// (ms; 26,805 tokens, d = 4096): fused projection 2.21 -> 1.97, O 0.78 ->
+// 0.73, gate/up 4.73 -> 4.33 (1.33 -> 1.45 PFLOP/s), down 2.57 -> 2.32; e4m3,
+// 226,108 tokens, d = 8192: gate/up 166 -> 145 (1.28 -> 1.47 PFLOP/s), down
+// 88.6 -> 74.6.  Without the half-phase offset gate/up takes 5.36 ms; with
+// raised wave priority in the multiply 4.35.
+//
+// Copies: a slice is four half-slices (A0 | A1: rows 0-63 | 64-127 of each
+// group's 128; B0 | B1: columns 0-31 | 32-63 of each wave's 64) in two LDS
+// buffers.  Phase p's reads and its issued copy (t = the current slice):
+//   p0: reads A0 of t      copies A1 of t + 1      quadrant (A0, B0)
+//   p1: reads B1 of t      copies B0 of t + 2      quadrant (A0, B1)
+//   p2: reads A1 of t      copies A0 of t + 2      quadrant (A1, B1)
+//   p3: reads B0 of t + 1  copies B1 of t + 2      quadrant (A1, B0)
+// (B0 is read a phase early, into a second register set, so no phase reads
+// more than the LDS delivers in the other group's multiply.)  A region is
+// overwritten two phases after its last read: the late group's reads have
+// then returned (it has passed its MFMAs of that phase).  Every copy has five
+// phases to land; a wave waits for its own copies (at most the five newest
+// half-slices in flight) before the barrier that opens the phase in which
+// they are read.
+template <int EPI, bool E4M3>
+__global__ void __launch_bounds__(512)
+gemm_mfma_256x256(int M, int N, int K, GemmA A, GemmB B, GemmC C, int k_per_split, int pid0) {
+    constexpr int BM = 256, BN = 256, FM = 8, FN = 4;
+    constexpr int ESZ = E4M3 ? 1 : 2, BROWB = BK * ESZ;
+    constexpr int A_HALF = 128 * 128, B_HALF = 128 * BROWB;
+    constexpr int BCP = B_HALF / 8192;               // 1 KiB copies per wave and half-slice (A: 2)
+    constexpr int BRPC = 1024 / BROWB;               // B rows per copy
+    // copies of the five newest half-slices after an A (B) half-slice's issue
+    constexpr int LEFT_A = 6 + 2 * BCP, LEFT_B = 4 + 3 * BCP;
+    constexpr int SLOTS = BROWB / 16;                // 16-byte chunks per B row
+    __shared__ __attribute__((aligned(16))) char lds[4 * A_HALF + 4 * B_HALF];
+
+    const int mt = (M + BM - 1) / BM, nt = N / BN;
+    int bx = 0, split = 0;
+    if (EPI == EPI_PARTIAL || EPI == EPI_PARTIAL_TILE) {   // see gemm_mfma_short
+        const int v = xcd_pid(blockIdx.x + blockIdx.y * gridDim.x, gridDim.x * gridDim.y);
+        split = v / gridDim.x;
+        bx = v - split * gridDim.x;
+    } else {
+        bx = xcd_pid(blockIdx.x, gridDim.x);
+        split = blockIdx.y;
+    }
+    const int tpid = pid0 + bx;
+    int tm, tn;
+    tile_coords(tpid, mt, nt, tm, tn);
+    const int m0 = tm * BM, n0 = tn * BN;
+    const int kb = split * k_per_split;
+    const int nk = max(0, (min(K, kb + k_per_split) - kb) / BK);
+
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wm = wave >> 2, wn = wave & 3;
+    const int grp = lane >> 4, l16 = lane & 15;
+
+    // copy sources (LDS slot lane % CH of a row holds chunk swz(row, slot));
+    // rows past M repeat row M - 1
+    const int a_rows = min(BM, M - m0);
+    // the K segments of A as a base and two byte steps (added below by
+    // uniform selects against 0)
+    const char* const a_base = static_cast<const char*>(A.p[0]) + (int64_t)m0 * A.ld * 2;
+    const int64_t a_step1 = A.p[1] ? static_cast<const char*>(A.p[1]) - static_cast<const char*>(A.p[0]) : 0;
+    const int64_t a_step2 = A.p[2] ? static_cast<const char*>(A.p[2]) - static_cast<const char*>(A.p[1]) : 0;
+    const int64_t a_bytes = ((int64_t)(a_rows - 1) * A.ld + A.kseg) * 2;
+    const int kseg = A.kseg;
+    __amdgpu_buffer_rsrc_t rb[2][BCP];
+    uint32_t va[2][2], vb[BCP];
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int r = wave * 16 + j * 8 + (lane >> 3);
+            const int row = (r >> 6) * 128 + h * 64 + (r & 63);
+            va[h][j] = static_cast<uint32_t>((min(row, a_rows - 1) * A.ld + swz_chunk<128>(r, lane & 7) * 8) * 2);
+        }
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int j = 0; j < BCP; ++j) {
+            const int r = wave * 16 + j * BRPC;                // a copy's rows share one 32-row block
+            const int w = r >> 5;
+            // LDS row r of a 32-row block is column 2 (r % 16) + r / 16 of it
+            const int c = 2 * (r & 15) + ((r >> 4) & 1);
+            const int n = EPI == EPI_QKV_ROPE ? n0 + (w >> 1) * 128 + h * 64 + (w & 1) * 32 + c : n0 + w * 64 + h * 32 + c;
+            int sg, row;
+            b_row(B, n, sg, row);
+            rb[h][j] = buf_rsrc(static_cast<const char*>(B.p[sg]) + (int64_t)row * B.ld * ESZ,
+                                ((int64_t)(2 * BRPC - 2) * B.ld + K) * ESZ);
+            const int lr = r + lane / SLOTS;
+            vb[j] = static_cast<uint32_t>((int64_t)(lane / SLOTS) * 2 * B.ld * ESZ + swz_chunk<BROWB>(lr, lane % SLOTS) * 16);
+        }
+    auto issue_a = [&](int t, int h) {
+        const int k0 = kb + min(t, nk - 1) * BK;               // past the end: a slice nobody reads
+        const int64_t step = (k0 >= kseg ? a_step1 : 0) + (k0 >= 2 * kseg ? a_step2 : 0);
+        const int ks = k0 - (k0 >= kseg ? kseg : 0) - (k0 >= 2 * kseg ? kseg : 0);
+        const __amdgpu_buffer_rsrc_t r = buf_rsrc(a_base + step, a_bytes);
+        char* base = lds + ((t & 1) * 2 + h) * A_HALF + wave * 2048;
+#pragma unroll
+        for (int j = 0; j < 2; ++j) dma16(r, va[h][j], base + j * 1024, static_cast<uint32_t>(ks * 2));
+    };
+    auto issue_b = [&](int t, int h) {
+        const int k0 = kb + min(t, nk - 1) * BK;
+        char* base = lds + 4 * A_HALF + ((t & 1) * 2 + h) * B_HALF + wave * (BCP * 1024);
+#pragma unroll
+        for (int j = 0; j < BCP; ++j) dma16(rb[h][j], vb[j], base + j * 1024, static_cast<uint32_t>(k0 * ESZ));
+    };
+
+    f32x4 acc[FM][FN];
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    // fragment addresses: A blocks of 16 rows are 2 KiB apart and share the
+    // swizzle; the two 32-deep steps of a slice differ in one chunk bit
+    // (b0: of even and odd slices).  e4m3 codes are widened only when they
+    // are multiplied, between the MFMAs: in the reading phase the widening
+    // would wait for the codes. 
+    typedef typename std::conditional<E4M3, u32x2, bf16x8>::type bfrag;
+    bf16x8 af[4][2];
+    bfrag b0[2][2][2], b1[2][2];
+    auto read_a = [&](int t, int h) {
+        const char* base = lds + ((t & 1) * 2 + h) * A_HALF;
+        const int row = wm * 64 + l16;
+#pragma unroll
+        for (int st = 0; st < 2; ++st)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                af[i][st] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(
+                                                           base + (row + 16 * i) * 128 + (swz_chunk<128>(row, 4 * st + grp) << 4)));
+    };
+    auto read_b = [&](int t, int h, bfrag (&bf)[2][2]) {
+        const char* base = lds + 4 * A_HALF + ((t & 1) * 2 + h) * B_HALF;
+#pragma unroll
+        for (int st = 0; st < 2; ++st)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const int row = wn * 32 + 16 * j + l16;
+                if constexpr (E4M3) {
+                    bf[j][st] = *reinterpret_cast<const u32x2*>(
+                        base + row * BROWB + (swz_chunk<BROWB>(row, 2 * st + (grp >> 1)) << 4) + 8 * (grp & 1));
+                } else {
+                    bf[j][st] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(
+                                                               base + row * BROWB + (swz_chunk<BROWB>(row, 4 * st + grp) << 4)));
+                }
+            }
+    };
+    auto multiply = [&](int hi, int hj, auto& braw) {
+        __builtin_amdgcn_sched_barrier(0);
+        barrier_no_fence();
+        __builtin_amdgcn_sched_barrier(0);
+        bf16x8 bf[2][2];
+#pragma unroll
+        for (int st = 0; st < 2; ++st)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                if constexpr (E4M3) {
+                    uint32_t w0, w1, w2, w3;
+                    e4m3x4_to_bf16x4(braw[j][st].x, w0, w1);
+                    e4m3x4_to_bf16x4(braw[j][st].y, w2, w3);
+                    bf[j][st] = __builtin_bit_cast(bf16x8, make_uint4(w0, w1, w2, w3));
+                } else {
+                    bf[j][st] = braw[j][st];
+                }
+            }
+#pragma unroll
+        for (int st = 0; st < 2; ++st)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+                    acc[4 * hi + i][2 * hj + j] =
+                        __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i][st], bf[j][st], acc[4 * hi + i][2 * hj + j], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // p3's reads are multiplied only in the next phase
+        barrier_no_fence();
+        __builtin_amdgcn_sched_barrier(0);
+    };
+
+    if (nk > 0) {
+        issue_b(0, 0); issue_a(0, 0); issue_b(0, 1); issue_a(0, 1); issue_b(1, 0); issue_a(1, 0); issue_b(1, 1);
+        wait_dma<LEFT_A>();      // B0 of slice 0 (the five newest may be in flight, and A0)
+        barrier_no_fence();
+        read_b(0, 0, b0[0]);
+        wait_dma<LEFT_B>();      // A0 of slice 0
+        barrier_no_fence();
+        if (wm == 1) barrier_no_fence();
+        auto slice = [&](int t, bfrag (&bc)[2][2], bfrag (&bn)[2][2]) {
+            read_a(t, 0);
+            issue_a(t + 1, 1);
+            wait_dma<LEFT_A>();  // B1 of t
+            multiply(0, 0, bc);
+            read_b(t, 1, b1);
+            issue_b(t + 2, 0);
+            wait_dma<LEFT_B>();  // A1 of t
+            multiply(0, 1, b1);
+            read_a(t, 1);
+            issue_a(t + 2, 0);
+            wait_dma<LEFT_A>();  // B0 of t + 1
+            multiply(1, 1, b1);
+            read_b(t + 1, 0, bn);
+            issue_b(t + 2, 1);
+            wait_dma<LEFT_B>();  // A0 of t + 1
+            multiply(1, 0, bc);
+        };
+        int t = 0;
+        for (; t + 1 < nk; t += 2) {
+            slice(t, b0[0], b0[1]);
+            slice(t + 1, b0[1], b0[0]);
+        }
+        if (t < nk) slice(t, b0[0], b0[1]);
+        if (wm == 0) barrier_no_fence();
+        wait_dma<0>();   // no LDS copy may outlive the workgroup
+    }
+    gemm_epilogue_pairs<EPI, E4M3>(acc, M, B, C, m0, n0, wm * 128, wn * 64, split,
+                                         (int64_t)split * gridDim.x + (tpid - pid0));
 }
 
 // ---------------------------------------------------------------- tail reduce
@@ -851,33 +1122,19 @@ void launch_tiles(int M, int N, int K, const GemmA& a, const GemmB& b, const Gem
     // slices in flight (the weight stream is what such calls wait on)
     if constexpr (EPI != EPI_QKV_ROPE && EPI != EPI_PARTIAL_TILE && OUTLETS_GEMM_SKINNY > 0) {
         if (gemm_bm(M, N, EPI) == 64) {
-            hipLaunchKernelGGL((gemm_mfma_256x256<EPI, E4M3, false, 1, 4, OUTLETS_GEMM_BK, OUTLETS_GEMM_SKINNY>),
+            hipLaunchKernelGGL((gemm_mfma_short<EPI, E4M3, 1, OUTLETS_GEMM_SKINNY>),
                                dim3(ntiles, splits), dim3(256), 0, st, M, N, K, a, b, c, kps, pid0);
             return;
         }
     }
     if constexpr (EPI != EPI_QKV_ROPE && EPI != EPI_PARTIAL_TILE && OUTLETS_GEMM_MID > 0) {
         if (gemm_bm(M, N, EPI) == 128) {
-            hipLaunchKernelGGL((gemm_mfma_256x256<EPI, E4M3, false, 2, 4, OUTLETS_GEMM_BK, OUTLETS_GEMM_MIDST>),
+            hipLaunchKernelGGL((gemm_mfma_short<EPI, E4M3, 2, OUTLETS_GEMM_MIDST>),
                                dim3(ntiles, splits), dim3(512), 0, st, M, N, K, a, b, c, kps, pid0);
             return;
         }
     }
-    // A-row prefetch for narrow outputs over many row tiles (measured on the
-    // d = 4096 draft layer: fused projection, O and down 3-9% faster; 1-3%
-    // slower for N = 28,672 and 7% slower for the QKV GEMM with its RoPE
-    // epilogue)
-    const bool pf = EPI != EPI_QKV_ROPE && N / 256 < 64 && (M + 255) / 256 >= 8;
-    if (pf)
-        hipLaunchKernelGGL((gemm_mfma_256x256<EPI, E4M3, true, OUTLETS_GEMM_WM, OUTLETS_GEMM_WN,
-                                              OUTLETS_GEMM_BK, OUTLETS_GEMM_STAGES>),
-                           dim3(ntiles, splits), dim3(OUTLETS_GEMM_WM * OUTLETS_GEMM_WN * 64), 0, st, M, N, K,
-                           a, b, c, kps, pid0);
-    else
-        hipLaunchKernelGGL((gemm_mfma_256x256<EPI, E4M3, false, OUTLETS_GEMM_WM, OUTLETS_GEMM_WN,
-                                              OUTLETS_GEMM_BK, OUTLETS_GEMM_STAGES>),
-                           dim3(ntiles, splits), dim3(OUTLETS_GEMM_WM * OUTLETS_GEMM_WN * 64), 0, st, M, N, K,
-                           a, b, c, kps, pid0);
+    hipLaunchKernelGGL((gemm_mfma_256x256<EPI, E4M3>), dim3(ntiles, splits), dim3(512), 0, st, M, N, K, a, b, c, kps, pid0);
 }
 
 // Compute units of the current device (cached per device).

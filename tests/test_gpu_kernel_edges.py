@@ -7,7 +7,7 @@ tolerance comes from.
 import numpy as np
 import pytest
 
-from gpu_common import (device_states, make_case, make_predictor, oracle_for, oracle_states, reduced_shape, rel_fro,
+from gpu_common import (TOL_HDRAFT, TOL_Z, device_states, make_case, make_predictor, oracle_for, oracle_states, reduced_shape, rel_fro,
                         require_gpu, say, step_inputs, tensor_to_f64, z_errors)
 
 pytestmark = pytest.mark.gpu
@@ -59,3 +59,21 @@ def test_fp32_gemm_tile_sizes(tokens, aligned):
     say(f"case: fp32 layer d={shape['d']}, {tokens} tokens in {len(lens)} requests, 1 step")
     case = make_case(0, lens=lens, shape=reduced_shape(**shape), n_req=len(lens))
     _against_oracle(case, sorted({0, len(lens) // 2, len(lens) - 1}), 1e-5, 1e-5)
+
+
+@pytest.mark.parametrize("cfg", [1, 4], ids=["bf16", "e4m3"])
+@pytest.mark.parametrize("tokens,requests", [(515, 3), (2050, 90), (16500, 620)])
+def test_large_tile_gemm_edges(cfg, tokens, requests):
+    """256-row tiles: K splits of one and of odd numbers of slices (515 and
+    2,050 rows; 620 requests give the head's K split one slice each), the
+    unsplit RoPE epilogue with prompts that start anywhere in the tile's
+    four-row groups, a ragged last row tile and a K-split last round (16,500
+    rows).  Tolerance: the repository's bounds for bf16 and e4m3 layers."""
+    r = np.random.default_rng(tokens)
+    cut = np.sort(r.choice(np.arange(1, tokens), requests - 1, replace=False))
+    lens = np.diff(np.concatenate([[0], cut, [tokens]]))
+    shape = reduced_shape(d=256, n_q=4, n_kv=2, ffn=640, head_hidden=256)
+    say(f"case: 256-row tiles, cfg {cfg}, {tokens} tokens in {requests} requests (longest {lens.max()}), 1 step")
+    case = make_case(cfg, lens=lens, shape=shape, n_req=requests)
+    sample = sorted({0, int(lens.argmax()), requests // 3, requests // 2, requests - 1})
+    _against_oracle(case, sample, TOL_HDRAFT[case.fmt], TOL_Z[case.fmt])

@@ -349,7 +349,7 @@ LayerGemms layer_gemms(const outlets_ctx* c, const CallBufs& b, const void* hl, 
 // for 1,024 rows is slower (the finish reads twice the partials).
 int head_splits(const outlets_ctx* c, int rows) {
     int s = kHeadSplits;
-    if (c->w_fmt == FMT_F32) return s;
+    if (c->w_fmt == FMT_F32 || gemm_streams(FMT_BF16, EPI_PARTIAL, rows, static_cast<int>(c->H1), static_cast<int>(2 * c->d))) return s;
     const int tiles = ((rows + 255) / 256) * static_cast<int>((c->H1 + 255) / 256);
     const int kslices = static_cast<int>(2 * c->d / 64);
     while (s < 32 && tiles * 2 * s <= gemm_device_cus() / 2 && kslices / (2 * s) >= 4) s *= 2;

@@ -825,6 +825,236 @@ gemm_mfma_256x256(int M, int N, int K, GemmA A, GemmB B, GemmC C, int k_per_spli
                                          (int64_t)split * gridDim.x + (tpid - pid0));
 }
 
+// ---------------------------------------------------------------- few rows
+// Calls of at most 16 MB activation rows stream the weights: each is
+// multiplied once per 16 rows and not needed again.  Weights go from HBM
+// straight into MFMA operands; activations, which every wave needs, go
+// through LDS.  A workgroup takes 16 RB NW weight rows on NW x KW waves (NW
+// along the rows, the KW waves of a row block taking every KW-th 64-deep
+// slice) over the K range of its split (blockIdx.y).  It walks K in chunks of
+// P slices per wave: a chunk's activations are copied by DMA while the one
+// before is multiplied (two buffers, one barrier per chunk; 16-byte piece c of
+// row r at c ^ (r % 16)), and each wave keeps a ring of P slices of weights in
+// flight, refilled as they are multiplied.  The KW sums meet in LDS in wave
+// order.
+//
+// k assignment: lane group g = lane / 16 holds k0 + 32 st + 8 g .. + 7 of a
+// slice in MFMA step st (bf16), or k0 + 16 g + 8 st .. + 7 (e4m3: one 16-byte
+// load of codes feeds both steps); weights and activations use the same.
+//
+// Weight rows of block rb: 16 consecutive ones; with EPI_SWIGLU (RB = 2) 16
+// gate and the matching 16 up rows; with EPI_QKV_ROPE channels c .. c + 7 and
+// c + 64 .. c + 71 of one head, so rotate-half pairs meet in one block.
+template <int EPI, bool E4M3, int MB, int RB, int NW, int P>
+__global__ void __launch_bounds__(512)
+gemm_stream(int M, int N, int K, GemmA A, GemmB B, GemmC C, int k_per_split) {
+    static_assert(EPI != EPI_SWIGLU || RB == 2, "gate and up blocks");
+    static_assert(EPI != EPI_QKV_ROPE || RB == 1, "half of each half of a head's 16 channels");
+    constexpr int KW = 8 / NW, ESZ = E4M3 ? 1 : 2, WL = E4M3 ? 1 : 2;   // WL: 16-byte weight loads per slice
+    constexpr int KC = KW * P * BK, ROW = KC * 2;                       // a chunk's k, bytes of a row
+    constexpr int ABUF = 16 * MB * ROW, CPW = ABUF / 8192;              // bytes per buffer, 1 KiB copies per wave
+    static_assert(KC % 256 == 0 && ABUF % 8192 == 0, "whole blocks and copies");
+    static_assert(2 * ABUF <= 128 * 1024, "two activation buffers");
+    constexpr int RED = KW > 1 ? 8 * RB * 16 * MB * 17 * 4 : 0;
+    __shared__ __attribute__((aligned(16))) char lds[2 * ABUF > RED ? 2 * ABUF : RED];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int grp = lane >> 4, l16 = lane & 15;
+    const int kw = wave % KW, nw = wave / KW;
+    const int blk0 = (blockIdx.x * NW + nw) * (EPI == EPI_SWIGLU ? 1 : RB);   // this wave's first block
+    const int kb = blockIdx.y * k_per_split, ke = min(K, kb + k_per_split);
+    const int ns = max(0, ke - kb) / BK, nc = (ns + KW * P - 1) / (KW * P);   // slices and chunks
+
+    const char* wrow[RB];
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+        int sg = rb, r = blk0 * 16 + l16;
+        if (EPI == EPI_QKV_ROPE) b_row(B, (blk0 >> 3) * 128 + (blk0 & 7) * 8 + (l16 & 7) + (l16 >> 3) * 64, sg, r);
+        else if (EPI != EPI_SWIGLU) b_row(B, (blk0 + rb) * 16 + l16, sg, r);
+        wrow[rb] = static_cast<const char*>(B.p[sg]) + ((int64_t)r * B.ld + kb) * ESZ + grp * 16;
+    }
+    const char* const a_base = static_cast<const char*>(A.p[0]);
+    const int64_t a_step1 = A.p[1] ? static_cast<const char*>(A.p[1]) - static_cast<const char*>(A.p[0]) : 0;
+    const int64_t a_step2 = A.p[2] ? static_cast<const char*>(A.p[2]) - static_cast<const char*>(A.p[1]) : 0;
+    const int kseg = A.kseg;
+    // chunk c of the activations, in blocks of 256 k ([block][row][512 B], so a
+    // block lies in one K segment): copy j of wave w is two rows of a block,
+    // lane i half row i / 32, the piece that belongs in LDS piece i % 32.  k
+    // past the split stays in its last slice (not multiplied), rows past M
+    // repeat the last row.
+    const int64_t a_bytes = ((int64_t)(M - 1) * A.ld + kseg) * 2;
+    const int ld2 = static_cast<int>(A.ld) * 2;
+    auto copy_a = [&](int c) {
+        char* base = lds + (c & 1) * ABUF + wave * CPW * 1024;
+#pragma unroll
+        for (int j = 0; j < CPW; ++j) {
+            const int blk = (wave * CPW + j) / (8 * MB), row = (wave * CPW + j) % (8 * MB) * 2 + (lane >> 5);
+            const int k0 = kb + c * KC + blk * 256;
+            const int kc = min(k0, (ke - 1) & ~255);           // a block past the split: its last one
+            const int64_t step = (kc >= kseg ? a_step1 : 0) + (kc >= 2 * kseg ? a_step2 : 0);
+            const int ks = kc - (kc >= kseg ? kseg : 0) - (kc >= 2 * kseg ? kseg : 0);
+            const int pk = min(8 * ((lane & 31) ^ (row & 15)), ke - 8 - kc);
+            dma16(buf_rsrc(a_base + step, a_bytes), static_cast<uint32_t>(min(row, M - 1) * ld2 + pk * 2), base + j * 1024,
+                  static_cast<uint32_t>(ks * 2));
+        }
+    };
+    // slice u of this wave's chunk
+    auto local = [&](int u) { return u * KW + kw; };
+    // its weights; past the end a repeat, not multiplied
+    auto load = [&](int c, int u, u32x4 (&w)[RB][WL]) {
+        const int k0 = min(c * (P * KW) + local(u), ns - 1) * BK;
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+            for (int q = 0; q < WL; ++q)
+                w[rb][q] = *reinterpret_cast<const u32x4*>(wrow[rb] + k0 * ESZ + 64 * q);
+    };
+    f32x4 acc[MB][RB];
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) acc[mb][rb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    auto multiply = [&](int c, int u, const u32x4 (&f)[RB][WL]) {
+        const int sl = local(u);                               // slice of the chunk
+        const char* base = lds + (c & 1) * ABUF + (sl >> 2) * (MB * 8192) + l16 * 512;
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const int pc = ((sl & 3) * 8 + (E4M3 ? 2 * grp + q : 4 * q + grp)) ^ l16;
+            bf16x8 w[RB];
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb) {
+                if constexpr (E4M3) {
+                    uint32_t w0, w1, w2, w3;
+                    e4m3x4_to_bf16x4(f[rb][0][2 * q], w0, w1);
+                    e4m3x4_to_bf16x4(f[rb][0][2 * q + 1], w2, w3);
+                    w[rb] = __builtin_bit_cast(bf16x8, u32x4{w0, w1, w2, w3});
+                } else {
+                    w[rb] = __builtin_bit_cast(bf16x8, f[rb][q]);
+                }
+            }
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb) {
+                const bf16x8 a = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(base + mb * 8192 + pc * 16));
+#pragma unroll
+                for (int rb = 0; rb < RB; ++rb)
+                    acc[mb][rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, w[rb], acc[mb][rb], 0, 0, 0);
+            }
+        }
+    };
+    if (ns > 0) {
+        u32x4 w[P][RB][WL];
+        copy_a(0);
+#pragma unroll
+        for (int u = 0; u < P; ++u) load(0, u, w[u]);
+        // One chunk; FULL: every slice exists (no branches, so the compiler
+        // counts the loads in flight).
+        auto chunk = [&](int c, auto full_tag) {
+            constexpr bool FULL = decltype(full_tag)::value;
+            // this wave's copies of chunk c are older than the ring's loads
+            wait_dma<P * RB * WL>();
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // chunk c - 1's reads have returned
+            barrier_no_fence();
+            copy_a(c + 1);                  // (past the end: into the buffer nobody reads again)
+#pragma unroll
+            for (int u = 0; u < P; ++u) {
+                if (FULL || c * (P * KW) + local(u) < ns) multiply(c, u, w[u]);
+                if (FULL) load(c + 1, u, w[u]);
+                __builtin_amdgcn_sched_barrier(0);     // refill each slot at once
+            }
+        };
+        const int nf = ns / (KW * P);
+        for (int c = 0; c < nf; ++c) chunk(c, std::true_type{});
+        if (nf < nc) chunk(nf, std::false_type{});
+        wait_dma<0>();                      // no copy may outlive the workgroup
+    }
+    auto scale = [&](int sg, int r) { return E4M3 ? bf16_to_f32(B.scale[sg][r]) : 1.f; };
+    // one output: block-local column cl of block `blk`, row m
+    auto store = [&](int blk, int m, int cl, float v, float u) {
+        const int n = blk * 16 + cl;
+        int sg = 0, r = n;
+        if (EPI != EPI_SWIGLU) b_row(B, n, sg, r);
+        v *= scale(sg, r);
+        if constexpr (EPI == EPI_SWIGLU) {
+            static_cast<bf16_t*>(C.c)[(int64_t)m * C.ldc + n] = f32_to_bf16(silu_f(v) * (u * scale(1, r)));
+        } else if constexpr (EPI == EPI_STORE_ACT) {
+            static_cast<bf16_t*>(C.c)[(int64_t)m * C.ldc + n] = f32_to_bf16(v);
+        } else {
+            float* c = static_cast<float*>(C.c) + (EPI == EPI_PARTIAL ? blockIdx.y * C.split_stride : 0);
+            c[(int64_t)m * C.ldc + n] = (EPI == EPI_RESID_F32 ? C.resid[(int64_t)m * C.ldr + n] : 0.f) + v;
+        }
+    };
+    auto store_rope = [&](int blk, int t, int cl, float x1, float x2) {
+        const RopeKV& R = C.rope;
+        const int head = blk >> 3, c = (blk & 7) * 8 + cl;
+        const int region = head < R.n_q ? 0 : (head < R.n_q + R.n_kv ? 1 : (head < R.n_q + 2 * R.n_kv ? 2 : 3));
+        const int kvh = region == 1 ? head - R.n_q : head - R.n_q - R.n_kv;
+        int sg, r;
+        b_row(B, head * 128 + c, sg, r);
+        x1 *= scale(sg, r);
+        x2 *= scale(sg, r + 64);
+        bf16_t* dst = static_cast<bf16_t*>(C.c) + (int64_t)t * C.ldc + head * 128;
+        if (region == 3) {
+            dst[c] = f32_to_bf16(x1);
+            dst[c + 64] = f32_to_bf16(x2);
+            return;
+        }
+        const int pos = R.tok_pos[t];
+        if (region > 0) {
+            const int page = R.page_table[(int64_t)R.tok_slot[t] * R.max_pages + (pos >> 4)];
+            if (region == 2) {
+                bf16_t* vb = R.vpool + ((int64_t)page * R.n_kv + kvh) * 128 * 16 + (pos & 15);
+                vb[c * 16] = f32_to_bf16(x1);
+                vb[(c + 64) * 16] = f32_to_bf16(x2);
+                return;
+            }
+            dst = R.kpool + (((int64_t)page * R.n_kv + kvh) * 16 + (pos & 15)) * 128;
+        }
+        const float cs = R.cos_t[(int64_t)pos * 64 + c], sn = R.sin_t[(int64_t)pos * 64 + c];
+        dst[c] = f32_to_bf16(x1 * cs - x2 * sn);
+        dst[c + 64] = f32_to_bf16(x2 * cs + x1 * sn);
+    };
+    if constexpr (KW == 1) {
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int m = mb * 16 + 4 * grp + e;
+                if constexpr (EPI == EPI_QKV_ROPE) {
+                    const float x2 = __shfl_xor(acc[mb][0][e], 8, 64);
+                    if (m < M && l16 < 8) store_rope(blk0, m, l16, acc[mb][0][e], x2);
+                } else {
+                    if (m >= M) continue;
+#pragma unroll
+                    for (int rb = 0; rb < (EPI == EPI_SWIGLU ? 1 : RB); ++rb)
+                        store(blk0 + rb, m, l16, acc[mb][rb][e], acc[mb][RB - 1][e]);
+                }
+            }
+    } else {
+        typedef float (*Red)[RB][16 * MB][17];      // [wave][block][row][column]
+        Red red = reinterpret_cast<Red>(lds);
+        barrier_no_fence();                          // every wave is done with the activations
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) red[wave][rb][mb * 16 + 4 * grp + e][l16] = acc[mb][rb][e];
+        __syncthreads();
+        auto total = [&](int w, int rb, int m, int c) {
+            float v = 0.f;
+#pragma unroll
+            for (int p = 0; p < KW; ++p) v += red[w * KW + p][rb][m][c];
+            return v;
+        };
+        constexpr int OB = EPI == EPI_SWIGLU ? 1 : RB, CL = EPI == EPI_QKV_ROPE ? 8 : 16;
+        for (int i = threadIdx.x; i < M * NW * OB * CL; i += 512) {
+            const int cl = i % CL, rb = (i / CL) % OB, w = (i / (CL * OB)) % NW, m = i / (CL * OB * NW);
+            const int blk = (blockIdx.x * NW + w) * OB + rb;
+            if constexpr (EPI == EPI_QKV_ROPE) store_rope(blk, m, cl, total(w, 0, m, cl), total(w, 0, m, cl + 8));
+            else store(blk, m, cl, total(w, rb, m, cl), EPI == EPI_SWIGLU ? total(w, RB - 1, m, cl) : 0.f);
+        }
+    }
+}
+
 // ---------------------------------------------------------------- tail reduce
 // The last tiles of a large GEMM (fewer than the CUs) run as S K-splits into
 // per-tile fp32 blocks ws[s][t][256][256], t = pid - pid0; this sums the S
@@ -1114,6 +1344,44 @@ int gemm_bm(int M, int N, int epi) {
     return 256;
 }
 
+// Waves of gemm_stream along the weight rows (of 8): 4 for bf16, whose
+// activations are then read from L2 by a quarter of the workgroups that 16
+// rows each would take; 8 for e4m3, where they are twice the weights' bytes.
+// The RoPE epilogue takes half, so that q|k|v still gives enough workgroups
+// without a split; so does a K split that would leave CUs idle (the length
+// head).
+int stream_waves(bool e4m3, int epi, int N, int splits) {
+    const int nw = e4m3 ? 8 : 4;
+    if (epi == EPI_QKV_ROPE || (epi == EPI_PARTIAL && N / (16 * nw) * splits < device_cus())) return nw / 2;
+    return nw;
+}
+
+template <int EPI, bool E4M3, int NW>
+void launch_stream_nw(int M, int N, int K, const GemmA& a, const GemmB& b, const GemmC& c, int splits, hipStream_t st) {
+    constexpr int RB = EPI == EPI_SWIGLU ? 2 : 1;
+    const int kps = ((K + splits - 1) / splits + 255) / 256 * 256;   // whole blocks of the activations
+    const dim3 grid(N / (16 * RB * NW), splits);
+    // weight slices in flight per wave: 2 (2 KiB each) for bf16, 8 (1 KiB)
+    // for e4m3.  More in flight is slower for bf16 (fused projection of 16
+    // rows with 2 / 4 / 8: 21.3 / 22.0 / 24.4 us).
+    constexpr int P = E4M3 ? 8 : 2, KW = 8 / NW, P4 = P * KW * 4 > 32 ? 32 / (KW * 4) : P;
+#define OUTLETS_STREAM(MB, PP) \
+    hipLaunchKernelGGL((gemm_stream<EPI, E4M3, MB, RB, NW, PP>), grid, dim3(512), 0, st, M, N, K, a, b, c, kps)
+    if (M <= 16) OUTLETS_STREAM(1, P);
+    else if (M <= 32) OUTLETS_STREAM(2, P);
+    else OUTLETS_STREAM(4, P4);
+#undef OUTLETS_STREAM
+}
+
+template <int EPI, bool E4M3>
+void launch_stream(int M, int N, int K, const GemmA& a, const GemmB& b, const GemmC& c, int splits, hipStream_t st) {
+    constexpr int NW = E4M3 ? 8 : 4;
+    if constexpr (EPI != EPI_QKV_ROPE)
+        if (stream_waves(E4M3, EPI, N, splits) == NW) return launch_stream_nw<EPI, E4M3, NW>(M, N, K, a, b, c, splits, st);
+    if constexpr (EPI == EPI_QKV_ROPE || EPI == EPI_PARTIAL)
+        launch_stream_nw<EPI, E4M3, NW / 2>(M, N, K, a, b, c, splits, st);
+}
+
 template <int EPI, bool E4M3>
 void launch_tiles(int M, int N, int K, const GemmA& a, const GemmB& b, const GemmC& c, int splits,
                   int pid0, int ntiles, hipStream_t st) {
@@ -1161,6 +1429,15 @@ struct SplitPlan {
 
 SplitPlan split_plan(int w_fmt, int epi, int M, int N, int K, int splits, size_t ws_bytes) {
     SplitPlan p{1, 1, 0, 0};
+    if (gemm_streams(w_fmt, epi, M, N, K)) {
+        const int sk = splits == 1 ? gemm_splitk_plan(w_fmt, epi, M, N, K) : 1;
+        const size_t need = (size_t)sk * M * N * sizeof(float);
+        if (sk > 1 && need <= ws_bytes) {
+            p.sk = sk;
+            p.bytes = need;
+        }
+        return p;
+    }
     if (splits == 1) {
         const int sk = gemm_splitk_plan(w_fmt, epi == EPI_QKV_ROPE ? EPI_STORE_ACT : epi, M, N, K);
         const size_t need = (size_t)sk * M * N * sizeof(float);
@@ -1196,6 +1473,10 @@ template <int EPI, bool E4M3>
 void launch_mfma(int act_fmt, int M, int N, int K, const GemmA& a, const GemmB& b,
                  const GemmC& c, int splits, hipStream_t st, float* ws, const SplitPlan& pl) {
     (void)act_fmt;
+    if (gemm_streams(E4M3 ? FMT_E4M3 : FMT_BF16, b.paired ? EPI_SWIGLU : EPI, M, N, K)) {
+        launch_stream<EPI, E4M3>(M, N, K, a, b, c, splits, st);
+        return;
+    }
     const int bm = gemm_bm(M, N, EPI);
     const int mt = (M + bm - 1) / bm, nt = N / 256, T = mt * nt;
     const int S = pl.tail_s, tail = pl.tail;
@@ -1242,25 +1523,55 @@ void launch_f32(int M, int N, int K, const GemmA& a, const GemmB& b, const GemmC
 
 }  // namespace
 
+// Up to 64 rows the few-row kernel, where its workgroups (before any K split)
+// fit the CUs in one round: 224 for the d = 4096 gate/up, 192 for q|k|v; the
+// 501-tile draft model head takes 176 us on 64 x 256 tiles and 216 here, a
+// 10,240-row q|k|v|gate of K = 8192 37 and 55.  With bf16 weights the gate/up
+// GEMM of more than 16 rows stays on the tiles too.  Measured against 64 x
+// 256 tiles with their reduces (d = 4096 bf16, 16 / 64 rows, us): fused
+// projection 25.0 / 29.3 -> 21.3 / 27.0, QKV 20.6 / 25.9 -> 19.3 / 24.0, O 13.9 /
+// 17.8 -> 10.2 / 13.2, down 25.3 / 31.5 -> 23.9 / 31.6, length head 17.1 / 18.3 ->
+// 12.5 / 19.7, the two norms and the pooling (fewer partials to add) 26.0 /
+// 26.7 -> 15.5 / 16.3; gate/up 45.0 / 48.0 -> 46.9 / 60.1; d = 8192 e4m3, 16 / 32
+// rows: fused 72.5 / 75.4 -> 42.6 / 49.1, gate/up 174 / 171 -> 108 / 118, down 70.1 /
+// 72.0 -> 46.7 / 53.8.  Matrices below 4M weights take about 1 us to read, so
+// there is nothing to stream, and on the tiled kernels a request's result
+// does not depend on the rows beside it.
+bool gemm_streams(int w_fmt, int epi, int M, int N, int K) {
+    if (w_fmt == FMT_F32 || epi == EPI_PARTIAL_TILE || (int64_t)N * K < 1 << 22) return false;
+    if (M > (w_fmt == FMT_BF16 && epi == EPI_SWIGLU ? 16 : 64)) return false;
+    const int rows = (epi == EPI_SWIGLU ? 32 : 16) * stream_waves(w_fmt == FMT_E4M3, epi, N, device_cus());
+    return N / rows <= device_cus();
+}
+
 int gemm_device_cus() { return device_cus(); }
 
 int gemm_splitk_plan(int w_fmt, int epi, int M, int N, int K) {
     if (w_fmt == FMT_F32 || epi == EPI_PARTIAL) return 1;
+    const int W = device_cus();
+    if (gemm_streams(w_fmt, epi, M, N, K)) {
+        // enough splits to give every CU a workgroup, each of at least 1,024 k
+        const int groups = N / ((epi == EPI_SWIGLU ? 32 : 16) * stream_waves(w_fmt == FMT_E4M3, epi, N, 1));
+        return std::max(1, std::min({8, W / std::max(1, groups), K / 1024}));
+    }
     const int bm = gemm_bm(M, N, epi);
     const int tiles = ((M + bm - 1) / bm) * (N / 256);
-    const int W = device_cus();
     if (tiles >= W) return 1;
     // Cost in units of one tile's full-K pass: ceil(tiles * s / W) rounds of
     // 1/s of a pass, plus the fp32 partials written and re-read by the reduce
     // (2 * 4 B * M * N per split at ~5 TB/s against ~1.3 us per 64-deep K
     // slice of a 256-row tile; half that for 128-row tiles, while a 64-row
-    // tile's slice costs about as much, its weight stream being the same).
+    // tile's slice costs about as much, its weight stream being the same),
+    // plus about two slices per round for the workgroups' start and end
+    // (without it the gate/up GEMM of one row took 16 splits of 112 tiles, 7
+    // rounds, 63 us; two splits in one round take 40).
     const double alpha = 512.0 * M * N / (6.5e6 * K) * (bm == 128 ? 2.0 : 1.0);
     const int smax = std::min(16, std::max(1, (K / BK) / 4));   // keep >= 4 K slices per split
     int best = 1;
     double best_cost = 1.0;
     for (int sp = 2; sp <= smax; ++sp) {
-        const double cost = (double)((tiles * sp + W - 1) / W) / sp + alpha * sp;
+        const int rounds = (tiles * sp + W - 1) / W;
+        const double cost = (double)rounds / sp + alpha * sp + 2.0 * BK / K * (rounds - 1);
         if (cost < best_cost) { best = sp; best_cost = cost; }
     }
     return best;

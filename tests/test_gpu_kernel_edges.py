@@ -77,3 +77,17 @@ def test_large_tile_gemm_edges(cfg, tokens, requests):
     case = make_case(cfg, lens=lens, shape=shape, n_req=requests)
     sample = sorted({0, int(lens.argmax()), requests // 3, requests // 2, requests - 1})
     _against_oracle(case, sample, TOL_HDRAFT[case.fmt], TOL_Z[case.fmt])
+
+
+@pytest.mark.parametrize("cfg", [1, 4], ids=["bf16", "e4m3"])
+@pytest.mark.parametrize("rows", [1, 16, 17, 33, 64])
+def test_few_row_gemm_edges(cfg, rows):
+    """The few-row kernel: one to four 16-row blocks, full and ragged, K
+    ranges that end inside a chunk of activations (ffn 2,688 = 10.5 blocks of
+    256), K splits (the d-wide outputs) and the unsplit RoPE and SwiGLU
+    epilogues; prompts of one token, so that the prefill has `rows` rows too.
+    Tolerance: the repository's bounds for bf16 and e4m3 layers."""
+    shape = reduced_shape(d=2048, n_q=16, n_kv=4, ffn=2688, head_hidden=1024)
+    say(f"case: few rows, cfg {cfg}, {rows} requests, d=2048, 2 steps")
+    case = make_case(cfg, lens=[1] * rows, shape=shape, n_req=rows)
+    _against_oracle(case, sorted({0, rows // 2, rows - 1}), TOL_HDRAFT[case.fmt], TOL_Z[case.fmt], steps=2)

@@ -76,6 +76,14 @@ __device__ __forceinline__ int xcd_pid(int bid, int nb) {
     return (x < r ? x * (q + 1) : r * (q + 1) + (x - r) * q) + i;
 }
 
+// Where workgroup i of a few-row gate/up GEMM starts its walk over n slices
+// of K.  With every workgroup at the same k, the rows of the two large
+// matrices (strides a power of two or near it) fall on the same memory
+// channels or not by where the allocations lie: 44-62 us for the 32-row 8B
+// call from process to process, 43-45 with the starts spread; the other
+// GEMMs do not show it.
+__device__ __forceinline__ int k_turn(int i, int n) { return n > 0 ? (3 * i) % n : 0; }
+
 // LDS DMA through a raw buffer descriptor: each lane copies 16 bytes from
 // descriptor base + voff to lds_base + 16 * lane (buffer_load_dwordx4 ...
 // lds).  Offsets at or past the descriptor's size read as zero.  32-bit
@@ -386,10 +394,14 @@ gemm_mfma_short(int M, int N, int K, GemmA A, GemmB B, GemmC C, int k_per_split,
     // slice `it` is always (STAGES - 2) slices' worth.
     const int nk_loop = max(nk, 0);
     constexpr int OPS = ACP + BCP;   // copies per issued slice (issuing waves)
+    // gate/up: each column tile starts its walk over K elsewhere (k_turn)
+    constexpr bool TURN = EPI == EPI_SWIGLU || EPI == EPI_PARTIAL;
+    const int t0 = TURN && B.paired ? k_turn(tn, nk_loop) : 0;
+    auto turn = [&](int i) { return TURN ? (i + t0 < nk_loop ? i + t0 : i + t0 - nk_loop) : i; };
     if (nk_loop > 0) {
 #pragma unroll
         for (int p = 0; p < STAGES - 1; ++p)
-            issue(kb + min(p, nk_loop - 1) * BK, p);
+            issue(kb + turn(min(p, nk_loop - 1)) * BK, p);
     }
     for (int it = 0; it < nk_loop; ++it) {
         // this wave's copies of slice `it` landed (later slices' may be pending)
@@ -400,7 +412,7 @@ gemm_mfma_short(int M, int N, int K, GemmA A, GemmB B, GemmC C, int k_per_split,
         // With bf16 weights the copies go out first; with e4m3 weights after
         // the first 32-deep step's MFMAs (measured: the other order is 10%
         // slower for bf16 and 3-5% slower for e4m3)
-        const int k_next = kb + min(it + STAGES - 1, nk_loop - 1) * BK;
+        const int k_next = kb + turn(min(it + STAGES - 1, nk_loop - 1)) * BK;
         if (!E4M3) issue(k_next, (it + STAGES - 1) % STAGES);
         const char* base = lds + (it % STAGES) * STAGE;
         bf16x8 af[2][FM], bfr[2][FN];
@@ -883,8 +895,12 @@ gemm_stream(int M, int N, int K, GemmA A, GemmB B, GemmC C, int k_per_split) {
     // repeat the last row.
     const int64_t a_bytes = ((int64_t)(M - 1) * A.ld + kseg) * 2;
     const int ld2 = static_cast<int>(A.ld) * 2;
-    auto copy_a = [&](int c) {
-        char* base = lds + (c & 1) * ABUF + wave * CPW * 1024;
+    // gate/up: each workgroup starts its walk over the full chunks elsewhere (k_turn)
+    const int nf = ns / (KW * P), t0 = EPI == EPI_SWIGLU ? k_turn(blockIdx.x, nf) : 0;
+    auto turn = [&](int c) { return EPI == EPI_SWIGLU && c < nf ? (c + t0 < nf ? c + t0 : c + t0 - nf) : c; };
+    auto copy_a = [&](int nth) {
+        const int c = turn(nth);
+        char* base = lds + (nth & 1) * ABUF + wave * CPW * 1024;
 #pragma unroll
         for (int j = 0; j < CPW; ++j) {
             const int blk = (wave * CPW + j) / (8 * MB), row = (wave * CPW + j) % (8 * MB) * 2 + (lane >> 5);
@@ -901,7 +917,7 @@ gemm_stream(int M, int N, int K, GemmA A, GemmB B, GemmC C, int k_per_split) {
     auto local = [&](int u) { return u * KW + kw; };
     // its weights; past the end a repeat, not multiplied
     auto load = [&](int c, int u, u32x4 (&w)[RB][WL]) {
-        const int k0 = min(c * (P * KW) + local(u), ns - 1) * BK;
+        const int k0 = min(turn(c) * (P * KW) + local(u), ns - 1) * BK;
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
@@ -961,7 +977,6 @@ gemm_stream(int M, int N, int K, GemmA A, GemmB B, GemmC C, int k_per_split) {
                 __builtin_amdgcn_sched_barrier(0);     // refill each slot at once
             }
         };
-        const int nf = ns / (KW * P);
         for (int c = 0; c < nf; ++c) chunk(c, std::true_type{});
         if (nf < nc) chunk(nf, std::false_type{});
         wait_dma<0>();                      // no copy may outlive the workgroup

@@ -128,6 +128,8 @@ struct outlets_ctx {
     int64_t tiles_off = 0;       // offset of cu_tiles (prefill pooling) in d_meta
     int64_t lanes_off = 0;       // offset of the decode plan's range offsets in d_meta
     int32_t n_lanes = 0;         // decode page ranges (waves per KV head) of the current call
+    int32_t n_segs = 0;          // its partial records
+    bool decode_by_request = false;   // the current step's attention needs no plan
     int32_t n_tiles = 0;
 
     int32_t* h_stage[2] = {nullptr, nullptr};
@@ -455,7 +457,10 @@ int run_layer(outlets_ctx* c, const CallBufs& b, bool prefill, int n, int T, con
                              c->n_lanes, b.d_meta + c->lanes_off, b.qkv,
                              c->qkv_dim, b.attn, c->qdim, req_slot, req_start, c->page_table,
                              c->max_pages, c->kpool, c->vpool, c->cfg.n_q_heads, c->cfg.n_kv_heads,
-                             b.decode_part, gate, st);
+                             c->n_segs, b.decode_part, gate, st);
+      else if (!prefill && c->decode_by_request)
+          launch_attn_decode_request(n, b.qkv, c->qkv_dim, b.attn, c->qdim, req_slot, req_start, c->page_table,
+                                     c->max_pages, c->kpool, c->vpool, c->cfg.n_q_heads, c->cfg.n_kv_heads, gate, st);
       else
           launch_attn_paged(af, T, b.qkv, c->qkv_dim, b.attn, c->qdim, b.tok_slot, b.tok_pos,
                             c->page_table, c->max_pages, c->kpool, c->vpool, c->cfg.n_q_heads,
@@ -700,10 +705,13 @@ int predict_step_impl(outlets_ctx* ctx, bool noalloc, int32_t n_req, const int32
     // split-KV decode: the step's pages cut into equal contiguous ranges, one
     // per wave and KV head (segments and pieces, see attn_decode_plan)
     DecodePlan plan;
+    bool by_request = false;
     if (attn_prefill_mfma_supported(ctx->act_fmt, ctx->cfg.n_q_heads, ctx->cfg.n_kv_heads, ctx->cfg.head_dim)) {
         std::vector<int32_t> pages(n_req);
         for (int i = 0; i < n_req; ++i) pages[i] = (start[i] + 1 + 15) / 16;
-        attn_decode_plan(n_req, pages.data(), ctx->cfg.n_kv_heads, gemm_device_cus(), &plan);
+        by_request = attn_decode_by_request(n_req, pages.data(), ctx->cfg.n_kv_heads, gemm_device_cus());
+        // (the no-allocation step accepts by the plan's size either way)
+        if (!by_request || noalloc) attn_decode_plan(n_req, pages.data(), ctx->cfg.n_kv_heads, gemm_device_cus(), &plan);
     }
     CallBufs sb;
     const CallBufs* bufs = &ctx->cb;
@@ -720,11 +728,14 @@ int predict_step_impl(outlets_ctx* ctx, bool noalloc, int32_t n_req, const int32
         layout_step(ctx, n_req, n_records, meta_count, ws, static_cast<char*>(ctx->scratch), &sb);
         bufs = &sb;
     }
+    if (by_request) plan = DecodePlan{};
     std::vector<int32_t> updates;
     ctx->prof_phase = 1;
     rc = ctx->pager->step(n_req, slots, &updates, &why);
     if (rc) return fail(rc, why);
     ctx->n_lanes = plan.n_lanes;
+    ctx->n_segs = plan.n_segs;
+    ctx->decode_by_request = by_request;
     NoTiming nt(ctx, noalloc);
     rc = upload_meta(ctx, *bufs, n_req, off, slots, start, updates, plan.work, plan.cu_segs, plan.lanes, 4, st);
     if (rc == OUTLETS_OK)

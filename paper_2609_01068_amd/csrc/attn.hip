@@ -449,6 +449,100 @@ typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
+// K and V^T fragments of one page for KV head g: lane (col, grp) holds key col's
+// channels 32 b + 8 grp .. + 7 and, of channel 16 cb + col, keys 4 grp .. + 3.
+// K/V pages are read once per step: non-temporal loads (measured on this
+// access pattern, loads alone: 6.6 TB/s against 5.9 TB/s with ordinary
+// loads, which a plain sequential read of the pools does not beat).
+__device__ __forceinline__ void decode_load_page(const bf16_t* kpool, const bf16_t* vpool, int64_t page, int n_kv, int g,
+                                                 int col, int grp, uint4* kf, uint2* vf) {
+    constexpr int HD = 128;
+    const bf16_t* kb = kpool + (page * n_kv + g) * 16 * HD + col * HD + 8 * grp;
+    const bf16_t* vb = vpool + (page * n_kv + g) * HD * 16 + col * 16 + 4 * grp;
+#pragma unroll
+    for (int b = 0; b < HD / 32; ++b)
+        kf[b] = __builtin_bit_cast(uint4, __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(kb + 32 * b)));
+#pragma unroll
+    for (int cb = 0; cb < HD / 16; ++cb)
+        vf[cb] = __builtin_bit_cast(uint2, __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(vb + 16 * 16 * cb)));
+}
+
+// The G query heads of KV head g of request r (columns 0 .. G - 1 of 16).
+template <int G>
+__device__ __forceinline__ void decode_load_q(const bf16_t* q, int64_t ldq, int r, int g, int col, int grp, bf16x8* qb) {
+    constexpr int HD = 128;
+    const bf16_t* qrow = q + (int64_t)r * ldq + (int64_t)(g * G + min(col, G - 1)) * HD + 8 * grp;
+#pragma unroll
+    for (int b = 0; b < HD / 32; ++b) {
+        uint4 v = *reinterpret_cast<const uint4*>(qrow + 32 * b);
+        if (col >= G) v = make_uint4(0u, 0u, 0u, 0u);
+        qb[b] = __builtin_bit_cast(bf16x8, v);
+    }
+}
+
+// Adds page pi's 16 keys to the running softmax (m, l, o) of nkeys keys.
+__device__ __forceinline__ void decode_add_page(int pi, int nkeys, int grp, float qscale, const bf16x8* qb, const uint4* kf,
+                                                const uint2* vf, float& m, float& l, f32x4* o) {
+    constexpr int HD = 128;
+    f32x4 sc = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int b = 0; b < HD / 32; ++b)
+        sc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kf[b]), qb[b], sc, 0, 0, 0);
+    // lane: head col, keys 4 grp + i of this page; only the request's last
+    // page holds keys past the end (wave-uniform)
+    const int k0 = pi * 16 + 4 * grp;
+    const bool last = pi * 16 + 16 > nkeys;
+    if (last) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (k0 + i >= nkeys) sc[i] = -INFINITY;
+    }
+    float mx = fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3]));
+    mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    mx *= qscale;                                   // finite: key 16 pi < nkeys
+    // The reference max m moves only when the page's max exceeds it by
+    // more than 8 (probabilities then stay <= 2^8), so the rescaling of o
+    // and l is skipped, wave-uniformly, on most pages; o / l and the
+    // merge of the partial records do not depend on the reference.
+    const bool grow = mx > m + 8.f;
+    if (__any(grow)) {
+        const float mn = grow ? mx : m;
+        const float corr = fast_exp2(m - mn);
+        m = mn;
+        l *= corr;
+#pragma unroll
+        for (int cb = 0; cb < HD / 16; ++cb) o[cb] = o[cb] * corr;
+    }
+    // the probabilities enter the PV product as bf16 and the row sum adds
+    // the same bf16 values, so the output is a convex combination of the
+    // value rows
+    const float nm = -m;
+    float ps = 0.f;
+    s16x4 pb;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const uint16_t pv = f32_to_bf16(fast_exp2(fmaf(sc[i], qscale, nm)));
+        pb[i] = static_cast<short>(pv);
+        ps += bf16_to_f32(pv);
+    }
+    ps += __shfl_xor(ps, 16, 64);
+    ps += __shfl_xor(ps, 32, 64);
+    l += ps;
+    // value rows of keys past the end may hold stale data: zero them
+#pragma unroll
+    for (int cb = 0; cb < HD / 16; ++cb) {
+        uint2 vv = vf[cb];
+        if (last) {
+            if (k0 + 0 >= nkeys) vv.x &= 0xFFFF0000u;
+            if (k0 + 1 >= nkeys) vv.x &= 0x0000FFFFu;
+            if (k0 + 2 >= nkeys) vv.y &= 0xFFFF0000u;
+            if (k0 + 3 >= nkeys) vv.y &= 0x0000FFFFu;
+        }
+        o[cb] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4, vv), pb, o[cb], 0, 0, 0);
+    }
+}
+
 template <int G>
 __global__ void __launch_bounds__(64)
 attn_decode_mfma(const bf16_t* __restrict__ q, int64_t ldq, const int32_t* __restrict__ work,
@@ -499,15 +593,7 @@ attn_decode_mfma(const bf16_t* __restrict__ q, int64_t ldq, const int32_t* __res
         const int nkeys = req_start[r] + 1;            // cached keys plus the new token's
 
         bf16x8 qb[HD / 32];
-        {
-            const bf16_t* qrow = q + (int64_t)r * ldq + (int64_t)(g * G + min(col, G - 1)) * HD + 8 * grp;
-#pragma unroll
-            for (int b = 0; b < HD / 32; ++b) {
-                uint4 v = *reinterpret_cast<const uint4*>(qrow + 32 * b);
-                if (col >= G) v = make_uint4(0u, 0u, 0u, 0u);
-                qb[b] = __builtin_bit_cast(bf16x8, v);
-            }
-        }
+        decode_load_q<G>(q, ldq, r, g, col, grp, qb);
 
         // the piece's page ids, one per lane, fetched up front so the K/V loads of
         // a page never wait on its page-table entry
@@ -518,78 +604,11 @@ attn_decode_mfma(const bf16_t* __restrict__ q, int64_t ldq, const int32_t* __res
         constexpr int PPI = OUTLETS_DECODE_PPI;
         uint4 kc[PPI][HD / 32], kn[PPI][HD / 32];
         uint2 vc[PPI][HD / 16], vn[PPI][HD / 16];
-        // K/V pages are read once per step: non-temporal loads (measured on this
-        // access pattern, loads alone: 6.6 TB/s against 5.9 TB/s with ordinary
-        // loads, which a plain sequential read of the pools does not beat)
         auto load_page = [&](int pi, uint4* kf, uint2* vf) {
-            const int64_t page = __shfl(my_page, min(pi, p1 - 1) - p0, 64);
-            const bf16_t* kb = kpool + (page * n_kv + g) * 16 * HD + col * HD + 8 * grp;
-            const bf16_t* vb = vpool + (page * n_kv + g) * HD * 16 + col * 16 + 4 * grp;
-#pragma unroll
-            for (int b = 0; b < HD / 32; ++b)
-                kf[b] = __builtin_bit_cast(uint4, __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(kb + 32 * b)));
-#pragma unroll
-            for (int cb = 0; cb < HD / 16; ++cb)
-                vf[cb] = __builtin_bit_cast(uint2, __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(vb + 16 * 16 * cb)));
+            decode_load_page(kpool, vpool, __shfl(my_page, min(pi, p1 - 1) - p0, 64), n_kv, g, col, grp, kf, vf);
         };
         auto one_page = [&](int pi, const uint4* kf, const uint2* vf) {
-            f32x4 sc = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int b = 0; b < HD / 32; ++b)
-                sc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kf[b]), qb[b], sc, 0, 0, 0);
-            // lane: head col, keys 4 grp + i of this page; only the request's last
-            // page holds keys past the end (wave-uniform)
-            const int k0 = pi * 16 + 4 * grp;
-            const bool last = pi * 16 + 16 > nkeys;
-            if (last) {
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    if (k0 + i >= nkeys) sc[i] = -INFINITY;
-            }
-            float mx = fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3]));
-            mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-            mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-            mx *= qscale;                                   // finite: key 16 pi < nkeys
-            // The reference max m moves only when the page's max exceeds it by
-            // more than 8 (probabilities then stay <= 2^8), so the rescaling of o
-            // and l is skipped, wave-uniformly, on most pages; o / l and the
-            // merge of the partial records do not depend on the reference.
-            const bool grow = mx > m + 8.f;
-            if (__any(grow)) {
-                const float mn = grow ? mx : m;
-                const float corr = fast_exp2(m - mn);
-                m = mn;
-                l *= corr;
-#pragma unroll
-                for (int cb = 0; cb < HD / 16; ++cb) o[cb] = o[cb] * corr;
-            }
-            // the probabilities enter the PV product as bf16 and the row sum adds
-            // the same bf16 values, so the output is a convex combination of the
-            // value rows
-            const float nm = -m;
-            float ps = 0.f;
-            s16x4 pb;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const uint16_t pv = f32_to_bf16(fast_exp2(fmaf(sc[i], qscale, nm)));
-                pb[i] = static_cast<short>(pv);
-                ps += bf16_to_f32(pv);
-            }
-            ps += __shfl_xor(ps, 16, 64);
-            ps += __shfl_xor(ps, 32, 64);
-            l += ps;
-            // value rows of keys past the end may hold stale data: zero them
-#pragma unroll
-            for (int cb = 0; cb < HD / 16; ++cb) {
-                uint2 vv = vf[cb];
-                if (last) {
-                    if (k0 + 0 >= nkeys) vv.x &= 0xFFFF0000u;
-                    if (k0 + 1 >= nkeys) vv.x &= 0x0000FFFFu;
-                    if (k0 + 2 >= nkeys) vv.y &= 0xFFFF0000u;
-                    if (k0 + 3 >= nkeys) vv.y &= 0x0000FFFFu;
-                }
-                o[cb] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4, vv), pb, o[cb], 0, 0, 0);
-            }
+            decode_add_page(pi, nkeys, grp, qscale, qb, kf, vf, m, l, o);
         };
 #pragma unroll
         for (int u = 0; u < PPI; ++u) load_page(p0 + u, kc[u], vc[u]);
@@ -627,31 +646,136 @@ attn_decode_mfma(const bf16_t* __restrict__ q, int64_t ldq, const int32_t* __res
     if (staged >= 0) flush();
 }
 
+// Decode attention of requests with short caches: one workgroup of 8 waves per
+// (request, KV head), wave w the w-th eighth of the request's pages, states
+// merged through LDS in wave order.  No plan, no partial records and no merge
+// kernel; the ranges of attn_decode_mfma hold 16 pages, so a step of a few
+// short caches ran on a few dozen waves, each a chain of 16 page latencies.
+constexpr int kReqWaves = 8;
+
+template <int G>
+__global__ void __launch_bounds__(64 * kReqWaves)
+attn_decode_request(const bf16_t* __restrict__ q, int64_t ldq, bf16_t* __restrict__ out, int64_t ldo,
+                    const int32_t* __restrict__ req_slot, const int32_t* __restrict__ req_start,
+                    const int32_t* __restrict__ page_table, int max_pages, const bf16_t* __restrict__ kpool,
+                    const bf16_t* __restrict__ vpool, int n_kv, float qscale, const bf16_t* __restrict__ gate) {
+    constexpr int HD = 128, NW = kReqWaves;
+    const int r = blockIdx.x, g = blockIdx.y;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, col = lane & 15, grp = lane >> 4;
+    const int nkeys = req_start[r] + 1, np = (nkeys + 15) >> 4;       // cached keys plus the new token's
+    const int p0 = np * w / NW, p1 = np * (w + 1) / NW;               // at most 64 pages
+    const int my_page = p0 + lane < p1 ? page_table[(int64_t)req_slot[r] * max_pages + p0 + lane] : 0;
+    float m = -INFINITY, l = 0.f;
+    f32x4 o[HD / 16];
+#pragma unroll
+    for (int cb = 0; cb < HD / 16; ++cb) o[cb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (p0 < p1) {
+        uint4 kc[HD / 32], kn[HD / 32];
+        uint2 vc[HD / 16], vn[HD / 16];
+        auto load = [&](int pi, uint4* kf, uint2* vf) {
+            decode_load_page(kpool, vpool, __shfl(my_page, min(pi, p1 - 1) - p0, 64), n_kv, g, col, grp, kf, vf);
+        };
+        load(p0, kc, vc);
+        bf16x8 qb[HD / 32];
+        decode_load_q<G>(q, ldq, r, g, col, grp, qb);
+        for (int pi = p0; pi < p1; ++pi) {          // (two pages per trip: the same)
+            load(pi + 1, kn, vn);
+            decode_add_page(pi, nkeys, grp, qscale, qb, kc, vc, m, l, o);
+#pragma unroll
+            for (int b = 0; b < HD / 32; ++b) kc[b] = kn[b];
+#pragma unroll
+            for (int cb = 0; cb < HD / 16; ++cb) vc[cb] = vn[cb];
+        }
+    }
+    __shared__ float sm[NW][G], sl[NW][G];
+    __shared__ __attribute__((aligned(16))) float so[NW][G][HD];
+    if (col < G) {
+        if (grp == 0) { sm[w][col] = m; sl[w][col] = l; }
+#pragma unroll
+        for (int cb = 0; cb < HD / 16; ++cb) *reinterpret_cast<f32x4*>(&so[w][col][16 * cb + 4 * grp]) = o[cb];
+    }
+    __syncthreads();
+    for (int e = threadIdx.x; e < G * HD; e += 64 * NW) {
+        const int h = e / HD, c = e % HD;
+        float M = -INFINITY;
+#pragma unroll
+        for (int v = 0; v < NW; ++v) M = fmaxf(M, sm[v][h]);
+        float L = 0.f, O = 0.f;
+#pragma unroll
+        for (int v = 0; v < NW; ++v) {
+            const float f = fast_exp2(sm[v][h] - M);    // 0 for a wave without pages (m = -inf)
+            L = fmaf(sl[v][h], f, L);
+            O = fmaf(so[v][h][c], f, O);
+        }
+        float y = O / L;
+        if (gate) y *= sigmoid_f(bf16_to_f32(gate[(int64_t)r * ldq + (int64_t)(g * G + h) * HD + c]));
+        out[(int64_t)r * ldo + (int64_t)(g * G + h) * HD + c] = f32_to_bf16(y);
+    }
+}
+
 // Merge of a request's segment partials, in segment (page) order
-// (deterministic).  Grid (n_req, ceil(n_q / 8)), 256 threads: 32 threads per
-// query head, 4 channels each.  The segments' maxima give the common
-// reference M; segment c's o and l enter with weight 2^(m_c - M).
-__global__ void __launch_bounds__(256)
+// (deterministic).  Grid (n_req, ceil(n_q / 8)), RG x 256 threads: 32 threads
+// per query head, 4 channels each, in RG groups that take consecutive parts
+// of the records and are merged through LDS in order.  Within a group the
+// maxima give the common reference M; record c's o and l enter with weight
+// 2^(m_c - M).  Records are loaded eight at a time: one by one, on one group,
+// they cost a memory latency each (six requests of 3,000-16,000 tokens,
+// about 40 records each: attention and merge 88.7 us, now 57.5).
+template <int RG>
+__global__ void __launch_bounds__(256 * RG)
 attn_decode_combine(const int32_t* cu_segs, const float* part, int n_q, bf16_t* out, int64_t ldo,
                     const bf16_t* gate, int64_t ldg) {
     constexpr int HD = 128;
-    const int r = blockIdx.x, h = blockIdx.y * 8 + (threadIdx.x >> 5), ch = (threadIdx.x & 31) * 4;
-    if (h >= n_q) return;
-    const int c0 = cu_segs[r], c1 = cu_segs[r + 1];
-    float M = -INFINITY;
-    for (int c = c0; c < c1; ++c) M = fmaxf(M, part[((int64_t)c * n_q + h) * kDecodeRec]);
-    float L = 0.f;
+    const int rg = threadIdx.x >> 8, hl = (threadIdx.x >> 5) & 7, ln = threadIdx.x & 31, ch = ln * 4;
+    const int r = blockIdx.x, h = blockIdx.y * 8 + hl;
+    const bool live = h < n_q;
+    const int a0 = cu_segs[r], na = cu_segs[r + 1] - a0;
+    const int c0 = a0 + na * rg / RG, c1 = a0 + na * (rg + 1) / RG;
+    float M = -INFINITY, L = 0.f;
     f32x4 O = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll 4
-    for (int c = c0; c < c1; ++c) {
-        const float* rec = part + ((int64_t)c * n_q + h) * kDecodeRec;
-        const float2 ml = *reinterpret_cast<const float2*>(rec);
-        const f32x4 v = *reinterpret_cast<const f32x4*>(rec + 4 + ch);
-        const float f = fast_exp2(ml.x - M);
-        L = fmaf(ml.y, f, L);
+    if (live) {
+        for (int c = c0 + ln; c < c1; c += 32) M = fmaxf(M, part[((int64_t)c * n_q + h) * kDecodeRec]);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) O[j] = fmaf(v[j], f, O[j]);
+        for (int x = 1; x < 32; x <<= 1) M = fmaxf(M, __shfl_xor(M, x, 64));
+        for (int b = c0; b < c1; b += 8) {
+            float2 ml[8];
+            f32x4 v[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const float* rec = part + ((int64_t)min(b + j, c1 - 1) * n_q + h) * kDecodeRec;
+                ml[j] = *reinterpret_cast<const float2*>(rec);
+                v[j] = *reinterpret_cast<const f32x4*>(rec + 4 + ch);
+            }
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                if (b + j >= c1) break;
+                const float f = fast_exp2(ml[j].x - M);
+                L = fmaf(ml[j].y, f, L);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) O[e] = fmaf(v[j][e], f, O[e]);
+            }
+        }
     }
+    if constexpr (RG > 1) {
+        __shared__ float sm[RG][8], sl[RG][8];
+        __shared__ __attribute__((aligned(16))) float so[RG][8][HD];
+        if (ln == 0) { sm[rg][hl] = M; sl[rg][hl] = L; }
+        *reinterpret_cast<f32x4*>(&so[rg][hl][ch]) = O;
+        __syncthreads();
+        if (rg > 0) return;
+#pragma unroll
+        for (int k = 1; k < RG; ++k) M = fmaxf(M, sm[k][hl]);
+        L = 0.f;
+        O = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int k = 0; k < RG; ++k) {
+            const float f = fast_exp2(sm[k][hl] - M);   // 0 for a group without records
+            L = fmaf(sl[k][hl], f, L);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) O[e] = fmaf(so[k][hl][ch + e], f, O[e]);
+        }
+    }
+    if (!live) return;
     float y[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) y[j] = O[j] / L;
@@ -798,7 +922,7 @@ void attn_decode_plan(int n_req, const int32_t* pages, int n_kv, int cus, Decode
 void launch_attn_decode(int n_req, int n_pieces, const int32_t* work, const int32_t* cu_segs, int n_lanes,
                         const int32_t* lanes, const void* q, int64_t ldq, void* out, int64_t ldo,
                         const int32_t* req_slot, const int32_t* req_start, const int32_t* page_table, int max_pages,
-                        const void* kpool, const void* vpool, int n_q, int n_kv, float* part,
+                        const void* kpool, const void* vpool, int n_q, int n_kv, int n_segs, float* part,
                         const void* gate, hipStream_t st) {
     if (n_req <= 0 || n_pieces <= 0 || n_lanes <= 0) return;
     const int G = n_q / n_kv;
@@ -817,8 +941,48 @@ void launch_attn_decode(int n_req, int n_pieces, const int32_t* work, const int3
         OUTLETS_DEC_G(8)
     }
 #undef OUTLETS_DEC_G
-    hipLaunchKernelGGL(attn_decode_combine, dim3(n_req, (n_q + 7) / 8), dim3(256), 0, st, cu_segs, part, n_q,
-                       static_cast<bf16_t*>(out), ldo, static_cast<const bf16_t*>(gate), ldq);
+    // four record groups once requests have more than eight records on average
+    const dim3 grid(n_req, (n_q + 7) / 8);
+    if (n_segs > 8 * n_req)
+        hipLaunchKernelGGL((attn_decode_combine<4>), grid, dim3(1024), 0, st, cu_segs, part, n_q,
+                           static_cast<bf16_t*>(out), ldo, static_cast<const bf16_t*>(gate), ldq);
+    else
+        hipLaunchKernelGGL((attn_decode_combine<1>), grid, dim3(256), 0, st, cu_segs, part, n_q,
+                           static_cast<bf16_t*>(out), ldo, static_cast<const bf16_t*>(gate), ldq);
+}
+
+// Measured against the ranges with their merge (d = 4096, 8 KV heads; us): 8
+// requests of 40 tokens 21.3 -> 6.1, 24 of 9-50 24.1 -> 6.7, 24 of 700-900 29.8
+// -> 22.8, 130 of 9-50 29.5 -> 21.0; slower where the workgroups fill the chip
+// several times over or a request's pages are a long chain: 130 of 300-600
+// 64.9 -> 67.9, 512 of 40-60 51.4 -> 73.6, 512 of 300-600 218 -> 253, one of
+// 1,500 23.2 -> 27.9.
+bool attn_decode_by_request(int n_req, const int32_t* pages, int n_kv, int cus) {
+    int most = 0;
+    for (int i = 0; i < n_req; ++i) most = std::max(most, pages[i]);
+    const int64_t groups = (int64_t)n_req * n_kv;
+    return (most <= 64 && groups <= 2 * cus) || (most <= 8 && groups <= 6 * cus);
+}
+
+void launch_attn_decode_request(int n_req, const void* q, int64_t ldq, void* out, int64_t ldo, const int32_t* req_slot,
+                                const int32_t* req_start, const int32_t* page_table, int max_pages, const void* kpool,
+                                const void* vpool, int n_q, int n_kv, const void* gate, hipStream_t st) {
+    if (n_req <= 0) return;
+    const float qscale = 1.4426950408889634f / sqrtf(128.0f);
+#define OUTLETS_DEC_G(GG)                                                                             \
+    case GG:                                                                                          \
+        hipLaunchKernelGGL((attn_decode_request<GG>), dim3(n_req, n_kv), dim3(64 * kReqWaves), 0, st, \
+                           static_cast<const bf16_t*>(q), ldq, static_cast<bf16_t*>(out), ldo, req_slot, req_start, \
+                           page_table, max_pages, static_cast<const bf16_t*>(kpool),                  \
+                           static_cast<const bf16_t*>(vpool), n_kv, qscale, static_cast<const bf16_t*>(gate)); \
+        break;
+    switch (n_q / n_kv) {
+        OUTLETS_DEC_G(1)
+        OUTLETS_DEC_G(2)
+        OUTLETS_DEC_G(4)
+        OUTLETS_DEC_G(8)
+    }
+#undef OUTLETS_DEC_G
 }
 
 bool attn_supported(int n_q, int n_kv, int hd) {

@@ -187,8 +187,15 @@ int attn_decode_record_floats();
 void launch_attn_decode(int n_req, int n_pieces, const int32_t* work, const int32_t* cu_segs, int n_lanes,
                         const int32_t* lanes, const void* q, int64_t ldq, void* out, int64_t ldo,
                         const int32_t* req_slot, const int32_t* req_start, const int32_t* page_table, int max_pages,
-                        const void* kpool, const void* vpool, int n_q, int n_kv, float* part,
+                        const void* kpool, const void* vpool, int n_q, int n_kv, int n_segs, float* part,
                         const void* gate, hipStream_t st);
+// Whether a step of requests with these page counts (the step's token
+// included) takes launch_attn_decode_request instead: one workgroup per
+// (request, KV head), no plan and no partial records.  At most 512 pages.
+bool attn_decode_by_request(int n_req, const int32_t* pages, int n_kv, int cus);
+void launch_attn_decode_request(int n_req, const void* q, int64_t ldq, void* out, int64_t ldo, const int32_t* req_slot,
+                                const int32_t* req_start, const int32_t* page_table, int max_pages, const void* kpool,
+                                const void* vpool, int n_q, int n_kv, const void* gate, hipStream_t st);
 
 // Attention of each token's queries over its slot's cached keys 0..pos.
 void launch_attn_paged(int act_fmt, int ntok, const void* q, int64_t ldq, void* out,

@@ -91,3 +91,30 @@ def test_few_row_gemm_edges(cfg, rows):
     say(f"case: few rows, cfg {cfg}, {rows} requests, d=2048, 2 steps")
     case = make_case(cfg, lens=[1] * rows, shape=shape, n_req=rows)
     _against_oracle(case, sorted({0, rows // 2, rows - 1}), TOL_HDRAFT[case.fmt], TOL_Z[case.fmt], steps=2)
+
+
+@pytest.mark.parametrize("cfg,lens", [
+    (1, [1, 15, 16, 17, 500, 1007]),            # one workgroup per request: up to 64 pages, waves without pages
+    (1, [1007, 1023, 30]),                      # the step crosses 64 pages in one request: ranges instead
+    (4, [3, 64, 129, 250] * 3),                 # 8 query heads per KV head
+    (1, [5] * 150 + [110] * 20),                # 8 pages at most, hundreds of workgroups
+    (1, [4100, 40, 2000]),                      # more than 8 records per request: four merge groups
+], ids=["short", "at 64 pages", "gqa8", "many short", "many records"])
+def test_decode_attention_by_request_and_by_ranges(cfg, lens):
+    """Steps around the rule that picks one workgroup per request or page
+    ranges, and around the merge's record groups.  Tolerance: the
+    repository's bounds for bf16 and e4m3 layers."""
+    n_q, n_kv = (16, 2) if cfg == 4 else (8, 2)
+    say(f"case: decode attention, cfg {cfg}, {len(lens)} requests of up to {max(lens)} tokens, 2 steps")
+    case = make_case(cfg, lens=lens, shape=reduced_shape(n_q=n_q, n_kv=n_kv), n_req=len(lens))
+    sample = sorted({0, len(lens) // 2, len(lens) - 1, int(np.argmax(lens))})
+    _against_oracle(case, sample, TOL_HDRAFT[case.fmt], TOL_Z[case.fmt], steps=2)
+
+
+@pytest.mark.parametrize("lens", [[1], [33, 31, 64, 7], [40] * 129], ids=["1 tile", "ragged tiles", "258 tiles"])
+def test_final_norm_pooling_row_groups(lens):
+    """Pooling tiles of one row, of ragged row groups, and past the switch to
+    one group per tile (256 tiles).  Tolerance: the bf16 layer's bounds."""
+    say(f"case: pooling tiles, {len(lens)} requests of up to {max(lens)} tokens")
+    case = make_case(1, lens=lens, shape=reduced_shape(d=1024, n_q=8, n_kv=2, ffn=1024), n_req=len(lens))
+    _against_oracle(case, sorted({0, len(lens) // 2, len(lens) - 1}), TOL_HDRAFT["bf16"], TOL_Z["bf16"])

@@ -333,20 +333,34 @@ pool_tiles_kernel(int d, int n_req, const TH* h, int64_t ldh, const int32_t* req
     part[(int64_t)t * d + c] = s;
 }
 
+// Sum over each of the RG groups of 256 threads of a block.
+template <int RG>
+__device__ __forceinline__ float group_sum(float v, float* red, int rg) {
+    v = wave_sum(v);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+    __syncthreads();
+    v = red[4 * rg] + red[4 * rg + 1] + red[4 * rg + 2] + red[4 * rg + 3];
+    __syncthreads();
+    return v;
+}
+
 // The final RMSNorm fused with stage 1 of the prefill pooling (d = 1024 V):
-// tile t (as in pool_tiles_kernel) normalises its rows in order with the
-// arithmetic of rmsnorm_vec_kernel and sums them in row order into part[t],
-// so the sums are those of the unfused pair, bit for bit.  Normalised rows
+// tile t (as in pool_tiles_kernel) normalises its rows with the
+// arithmetic of rmsnorm_vec_kernel and sums them into part[t].  Normalised rows
 // are stored (y2 fp32, y in the act format) only when full_rows; otherwise
 // only each request's last row, which the head input also needs.  The next
 // row's loads are issued before the current row's reduction.
-template <typename TY, typename TG, int V>
-__global__ void __launch_bounds__(256)
+// RG row groups of 256 threads take every RG-th row of the tile and share
+// each reduction's barrier; their sums are added in group order.  Few tiles
+// leave most CUs idle and wait on 32 rows' latencies one after the other:
+// with RG = 4 on eight.
+template <typename TY, typename TG, int V, int RG>
+__global__ void __launch_bounds__(256 * RG)
 norm_pool_tiles_kernel(int d, int n_req, const float* x, int64_t ldx, const TG* gamma, float eps, TY* y,
                        int64_t ldy, float* y2, int64_t ldy2, int full_rows, const int32_t* req_off,
                        const int32_t* cu_tiles, float* part) {
-    __shared__ float red[4];
-    const int t = blockIdx.x, th = threadIdx.x;
+    __shared__ float red[4 * RG];
+    const int t = blockIdx.x, th = threadIdx.x & 255, rg = threadIdx.x >> 8;
     int lo = 0, hi = n_req - 1;        // request lo with cu_tiles[lo] <= t < cu_tiles[lo + 1]
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
@@ -372,9 +386,10 @@ norm_pool_tiles_kernel(int d, int n_req, const float* x, int64_t ldx, const TG* 
 #pragma unroll
     for (int j = 0; j < V; ++j) {
         acc[j] = make_float4(0.f, 0.f, 0.f, 0.f);
-        vn[j] = reinterpret_cast<const float4*>(x + (int64_t)b * ldx)[j * 256 + th];
+        vn[j] = reinterpret_cast<const float4*>(x + (int64_t)min(b + rg, e - 1) * ldx)[j * 256 + th];
     }
-    for (int r = b; r < e; ++r) {
+    for (int r0 = b; r0 < e; r0 += RG) {      // rows past the end repeat the last one, unused
+        const int r = r0 + rg;
         float4 v[V];
         float ss = 0.f;
 #pragma unroll
@@ -382,11 +397,12 @@ norm_pool_tiles_kernel(int d, int n_req, const float* x, int64_t ldx, const TG* 
             v[j] = vn[j];
             ss = fmaf(v[j].x, v[j].x, fmaf(v[j].y, v[j].y, fmaf(v[j].z, v[j].z, fmaf(v[j].w, v[j].w, ss))));
         }
-        if (r + 1 < e) {
+        if (r0 + RG < e) {
 #pragma unroll
-            for (int j = 0; j < V; ++j) vn[j] = reinterpret_cast<const float4*>(x + (int64_t)(r + 1) * ldx)[j * 256 + th];
+            for (int j = 0; j < V; ++j) vn[j] = reinterpret_cast<const float4*>(x + (int64_t)min(r + RG, e - 1) * ldx)[j * 256 + th];
         }
-        ss = block_sum<256>(ss, red);
+        ss = group_sum<RG>(ss, red, rg);
+        if (r >= e) continue;                 // (only in the last round)
         const float inv = 1.0f / sqrtf(ss / d + eps);
         const bool store = full_rows || r == last;
 #pragma unroll
@@ -409,6 +425,23 @@ norm_pool_tiles_kernel(int d, int n_req, const float* x, int64_t ldx, const TG* 
                 *reinterpret_cast<float4*>(y2 + (int64_t)r * ldy2 + c) = make_float4(o0, o1, o2, o3);
             }
         }
+    }
+    if constexpr (RG > 1) {
+        __shared__ float4 other[RG - 1][256];
+#pragma unroll
+        for (int j = 0; j < V; ++j) {
+            if (rg > 0) other[rg - 1][th] = acc[j];
+            __syncthreads();
+            if (rg == 0) {
+#pragma unroll
+                for (int k = 0; k < RG - 1; ++k) {
+                    const float4 v = other[k][th];
+                    acc[j].x += v.x; acc[j].y += v.y; acc[j].z += v.z; acc[j].w += v.w;
+                }
+            }
+            __syncthreads();
+        }
+        if (rg > 0) return;
     }
 #pragma unroll
     for (int j = 0; j < V; ++j) reinterpret_cast<float4*>(part + (int64_t)t * d)[j * 256 + th] = acc[j];
@@ -780,11 +813,21 @@ bool launch_norm_pool_prefill(int act_fmt, int gamma_fmt, int n_req, int n_tiles
     if (!vec) return false;
     if (n_req <= 0) return true;
     const int V = d / 1024, fr = full_rows ? 1 : 0;
+    // Up to one tile per CU: several row groups per tile.  Measured at d =
+    // 4096 with the second stage (one group / four, us): 25 tiles 34.9 / 21.7,
+    // 186 35.3 / 24.9, 400 53.2 / 54.9, 854 108.3 / 113.2.  (d = 8192: two
+    // groups; four of its 8 float4 per thread would spill.)
+    const bool few = n_tiles <= 256;
 #define OUTLETS_NP_V(TY, TG, VV)                                                                        \
     case VV:                                                                                            \
-        hipLaunchKernelGGL((norm_pool_tiles_kernel<TY, TG, VV>), dim3(n_tiles), dim3(256), 0, st, d, n_req, x, \
-                           ldx, static_cast<const TG*>(gamma), eps, static_cast<TY*>(y), ldy, y2, ldy2, fr,  \
-                           req_off, cu_tiles, part);                                                    \
+        if (few)                                                                                        \
+            hipLaunchKernelGGL((norm_pool_tiles_kernel<TY, TG, VV, (VV > 4 ? 2 : 4)>), dim3(n_tiles), dim3(VV > 4 ? 512 : 1024), 0, st, d, n_req, x, \
+                               ldx, static_cast<const TG*>(gamma), eps, static_cast<TY*>(y), ldy, y2, ldy2, fr, \
+                               req_off, cu_tiles, part);                                                \
+        else                                                                                            \
+            hipLaunchKernelGGL((norm_pool_tiles_kernel<TY, TG, VV, 1>), dim3(n_tiles), dim3(256), 0, st, d, n_req, x, \
+                               ldx, static_cast<const TG*>(gamma), eps, static_cast<TY*>(y), ldy, y2, ldy2, fr, \
+                               req_off, cu_tiles, part);                                                \
         break;
 #define OUTLETS_NP(TY, TG)                                                                              \
     switch (V) { OUTLETS_NP_V(TY, TG, 1) OUTLETS_NP_V(TY, TG, 2) OUTLETS_NP_V(TY, TG, 4) OUTLETS_NP_V(TY, TG, 8) }

@@ -1336,15 +1336,22 @@ gemm_f32_mfma(int M, int N, int K, GemmA A, GemmB B, GemmC C, int k_per_split) {
 #define OUTLETS_GEMM_MIDST 3    // LDS stages of the 128-row kernel
 #endif
 
-// Row-tile height for M rows and N columns: 64 up to 64 rows; 128 up to
-// OUTLETS_GEMM_MID rows when that takes no more rounds over the CUs than
+// Row-tile height for M rows, N columns and depth K: 64 up to 64 rows; 128 up
+// to OUTLETS_GEMM_MID rows when that takes no more rounds over the CUs than
 // 256-row tiles (measured at M = 256 and 512: 8-17% faster for N = 4096 and
 // 6,144, and for gate/up at M = 256; at M = 512 gate/up needs two rounds of
-// 128-row tiles and is 25% slower); else 256.  Always 256 for the QKV RoPE
-// epilogue (it needs 128-wide wave tiles) and the tail-split blocks.
+// 128-row tiles and is 25% slower); else 256.  Long K favours the 256-row
+// kernel's copies sooner: K > 8,192 from 257 rows (fused projection, d = 4096,
+// 128 / 256-row tiles, us: 300 rows 54.3 / 48.9, 512 rows 67.9 / 56.5; down 52.3
+// / 48.2, 67.2 / 56.3; at 130 rows its extra K splits cost the norms what it
+// gains), and so does e4m3, whose widening it halves, from 129 rows (d =
+// 8192, K >= 8192, 130 / 512 rows: fused 96.4 / 203 -> 82.2 / 149, QKV 56 / 121 ->
+// 53 / 94, O 38 / 74 -> 35 / 60, down 110 / 232 -> 86 / 171; gate/up 161 / 350 -> 170
+// / 349, which stays).  Always 256 for the QKV RoPE epilogue and the
+// tail-split blocks.
 int device_cus();
 
-int gemm_bm(int M, int N, int epi) {
+int gemm_bm(int w_fmt, int M, int N, int K, int epi, bool paired) {
     if (epi == EPI_QKV_ROPE || epi == EPI_PARTIAL_TILE) return 256;
     if (OUTLETS_GEMM_SKINNY > 0 && M <= 64) return 64;
     // explicit K splits of a narrow output up to 1,024 rows (the length
@@ -1352,6 +1359,8 @@ int gemm_bm(int M, int N, int epi) {
     // workgroups of 256-row ones, which left half the CUs idle (measured at
     // 1,024 x 1,024 with 8 splits: head GEMM + finish 41.5 -> 36.6 us)
     if (OUTLETS_GEMM_MID > 0 && epi == EPI_PARTIAL && M <= 2 * OUTLETS_GEMM_MID && N <= 1024) return 128;
+    if (!paired && epi != EPI_SWIGLU && N >= 4096 && (w_fmt == FMT_E4M3 ? M > 128 && K >= 8192 : M > 256 && K > 8192))
+        return 256;
     if (OUTLETS_GEMM_MID > 0 && M <= OUTLETS_GEMM_MID) {
         const int W = device_cus(), nt = N / 256;
         if ((((M + 127) / 128) * nt + W - 1) / W <= (((M + 255) / 256) * nt + W - 1) / W) return 128;
@@ -1401,17 +1410,18 @@ template <int EPI, bool E4M3>
 void launch_tiles(int M, int N, int K, const GemmA& a, const GemmB& b, const GemmC& c, int splits,
                   int pid0, int ntiles, hipStream_t st) {
     const int kps = ((K / BK + splits - 1) / splits) * BK;
+    const int bm = gemm_bm(E4M3 ? FMT_E4M3 : FMT_BF16, M, N, K, EPI, b.paired != 0);
     // At most 64 rows: 64 x 256 tiles on 4 waves of 64 x 64, with more K
     // slices in flight (the weight stream is what such calls wait on)
     if constexpr (EPI != EPI_QKV_ROPE && EPI != EPI_PARTIAL_TILE && OUTLETS_GEMM_SKINNY > 0) {
-        if (gemm_bm(M, N, EPI) == 64) {
+        if (bm == 64) {
             hipLaunchKernelGGL((gemm_mfma_short<EPI, E4M3, 1, OUTLETS_GEMM_SKINNY>),
                                dim3(ntiles, splits), dim3(256), 0, st, M, N, K, a, b, c, kps, pid0);
             return;
         }
     }
     if constexpr (EPI != EPI_QKV_ROPE && EPI != EPI_PARTIAL_TILE && OUTLETS_GEMM_MID > 0) {
-        if (gemm_bm(M, N, EPI) == 128) {
+        if (bm == 128) {
             hipLaunchKernelGGL((gemm_mfma_short<EPI, E4M3, 2, OUTLETS_GEMM_MIDST>),
                                dim3(ntiles, splits), dim3(512), 0, st, M, N, K, a, b, c, kps, pid0);
             return;
@@ -1467,7 +1477,7 @@ SplitPlan split_plan(int w_fmt, int epi, int M, int N, int K, int splits, size_t
     // last round holds only a few tiles, those tiles run instead as S K-splits
     // (S * tail <= W workgroups of 1/S the work) and are summed by
     // tile_reduce, so the last round costs about 1/S of a round.
-    const int bm = gemm_bm(M, N, epi);
+    const int bm = gemm_bm(w_fmt, M, N, K, epi, false);
     const int T = ((M + bm - 1) / bm) * (N / 256);
     const int W = device_cus();
     const int full = T / W, tail = T % W;
@@ -1492,7 +1502,7 @@ void launch_mfma(int act_fmt, int M, int N, int K, const GemmA& a, const GemmB& 
         launch_stream<EPI, E4M3>(M, N, K, a, b, c, splits, st);
         return;
     }
-    const int bm = gemm_bm(M, N, EPI);
+    const int bm = gemm_bm(E4M3 ? FMT_E4M3 : FMT_BF16, M, N, K, EPI, b.paired != 0);
     const int mt = (M + bm - 1) / bm, nt = N / 256, T = mt * nt;
     const int S = pl.tail_s, tail = pl.tail;
     if (S < 2) {
@@ -1569,7 +1579,7 @@ int gemm_splitk_plan(int w_fmt, int epi, int M, int N, int K) {
         const int groups = N / ((epi == EPI_SWIGLU ? 32 : 16) * stream_waves(w_fmt == FMT_E4M3, epi, N, 1));
         return std::max(1, std::min({8, W / std::max(1, groups), K / 1024}));
     }
-    const int bm = gemm_bm(M, N, epi);
+    const int bm = gemm_bm(w_fmt, M, N, K, epi, false);
     const int tiles = ((M + bm - 1) / bm) * (N / 256);
     if (tiles >= W) return 1;
     // Cost in units of one tile's full-K pass: ceil(tiles * s / W) rounds of

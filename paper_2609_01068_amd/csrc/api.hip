@@ -387,9 +387,10 @@ int check_gemms(const outlets_ctx* c) {
 }
 
 // Queue the draft layer + head for `T` tokens of `n` requests whose
-// metadata is already on the device.
-int run_layer(outlets_ctx* c, const CallBufs& b, bool prefill, int n, int T, const void* hl, const void* hm,
-              const void* hh, int64_t row_stride, const int32_t* tokens, float* z_out,
+// metadata is staged (mf); the first norm brings it to the device, and no
+// kernel before it reads any.
+int run_layer(outlets_ctx* c, const CallBufs& b, const MetaFetch& mf, bool prefill, int n, int T, const void* hl,
+              const void* hm, const void* hh, int64_t row_stride, const int32_t* tokens, float* z_out,
               void* hdraft_out, hipStream_t st) {
     const int af = c->act_fmt, wf = c->w_fmt;
     const int64_t d = c->d;
@@ -420,9 +421,12 @@ int run_layer(outlets_ctx* c, const CallBufs& b, bool prefill, int n, int T, con
     { KTimer t(c, OUTLETS_K_NORM, st);
       if (sk)
           launch_rmsnorm_sum(af, c->small_fmt, T, d, rowsum(sk, nullptr, b.r_f), c->w.gamma_attn, eps, b.a_norm, d,
-                             st);
+                             st, mf);
       else
-          launch_rmsnorm(af, c->small_fmt, T, d, b.r_f, d, c->w.gamma_attn, eps, b.a_norm, d, nullptr, 0, st);
+          launch_rmsnorm(af, c->small_fmt, T, d, b.r_f, d, c->w.gamma_attn, eps, b.a_norm, d, nullptr, 0, st, mf);
+      HIP_TRY(hipEventRecord(c->ev[c->stage], st), "hipEventRecord");   // the staging buffer is free again after this
+      c->ev_used[c->stage] = true;
+      c->stage ^= 1;
       if (c->embed_in)
           launch_embed_norm(af, c->small_fmt, T, static_cast<int>(d), c->cfg.vocab, tokens, c->w.embed,
                             c->w.gamma_emb, eps, b.e_norm, d, st); }
@@ -536,11 +540,11 @@ int run_layer(outlets_ctx* c, const CallBufs& b, bool prefill, int n, int T, con
     return OUTLETS_OK;
 }
 
-// Stage req_off | req_slot | req_start | updates into pinned memory and copy to the device.
-int upload_meta(outlets_ctx* c, const CallBufs& b, int n, const std::vector<int32_t>& off, const int32_t* slots,
-                const std::vector<int32_t>& start, const std::vector<int32_t>& updates,
-                const std::vector<int32_t>& work, const std::vector<int32_t>& cu_tiles,
-                const std::vector<int32_t>& lanes, int work_stride, hipStream_t st) {
+// Stage req_off | req_slot | req_start | updates in pinned memory, for the layer's first norm to fetch.
+int stage_meta(outlets_ctx* c, const CallBufs& b, int n, const std::vector<int32_t>& off, const int32_t* slots,
+               const std::vector<int32_t>& start, const std::vector<int32_t>& updates,
+               const std::vector<int32_t>& work, const std::vector<int32_t>& cu_tiles,
+               const std::vector<int32_t>& lanes, int work_stride, MetaFetch* mf) {
     const int64_t count = (n + 1) + 2 * static_cast<int64_t>(n) + static_cast<int64_t>(updates.size()) +
                           static_cast<int64_t>(work.size()) + static_cast<int64_t>(cu_tiles.size()) +
                           static_cast<int64_t>(lanes.size());
@@ -560,17 +564,10 @@ int upload_meta(outlets_ctx* c, const CallBufs& b, int n, const std::vector<int3
     if (!cu_tiles.empty()) std::memcpy(h + c->tiles_off, cu_tiles.data(), sizeof(int32_t) * cu_tiles.size());
     c->lanes_off = c->tiles_off + static_cast<int64_t>(cu_tiles.size());
     if (!lanes.empty()) std::memcpy(h + c->lanes_off, lanes.data(), sizeof(int32_t) * lanes.size());
-    {
-        // one kernel reads the staged block from host memory (no copy-engine
-        // transfer on the call's critical path), applies the page-table
-        // updates and builds the token arrays
-        KTimer t(c, OUTLETS_K_META, st);
-        launch_meta_fetch(h, static_cast<int>(count), n, static_cast<int>(updates.size() / 2), b.d_meta,
-                          c->page_table, b.tok_slot, b.tok_pos, b.last_idx, st);
-    }
-    HIP_TRY(hipEventRecord(c->ev[s], st), "hipEventRecord");
-    c->ev_used[s] = true;
-    c->stage ^= 1;
+    // the first norm of the layer reads the staged block (run_layer)
+    *mf = MetaFetch{h, static_cast<int>(count), n, static_cast<int>(updates.size() / 2),
+                    meta_fetch_blocks(static_cast<int>(count), n), b.d_meta, c->page_table, b.tok_slot, b.tok_pos,
+                    b.last_idx};
     return OUTLETS_OK;
 }
 
@@ -737,9 +734,10 @@ int predict_step_impl(outlets_ctx* ctx, bool noalloc, int32_t n_req, const int32
     ctx->n_segs = plan.n_segs;
     ctx->decode_by_request = by_request;
     NoTiming nt(ctx, noalloc);
-    rc = upload_meta(ctx, *bufs, n_req, off, slots, start, updates, plan.work, plan.cu_segs, plan.lanes, 4, st);
+    MetaFetch mf{};
+    rc = stage_meta(ctx, *bufs, n_req, off, slots, start, updates, plan.work, plan.cu_segs, plan.lanes, 4, &mf);
     if (rc == OUTLETS_OK)
-        rc = run_layer(ctx, *bufs, false, n_req, n_req, h_low, h_mid, h_high, row_stride, tokens, z_out,
+        rc = run_layer(ctx, *bufs, mf, false, n_req, n_req, h_low, h_mid, h_high, row_stride, tokens, z_out,
                        hdraft_out, st);
     if (rc) return rc;   // device work may be partly queued; the slot lengths advanced
     ctx->last_n = n_req;
@@ -979,9 +977,10 @@ int outlets_predict_prefill(outlets_ctx* ctx, int32_t n_req, const int32_t* slot
     }
     std::vector<int32_t> cu_tiles(n_req + 1, 0);
     for (int i = 0; i < n_req; ++i) cu_tiles[i + 1] = cu_tiles[i] + (lens[i] + 31) / 32;
-    rc = upload_meta(ctx, ctx->cb, n_req, off, slots, start, updates, work, cu_tiles, {}, 2, st);
+    MetaFetch mf{};
+    rc = stage_meta(ctx, ctx->cb, n_req, off, slots, start, updates, work, cu_tiles, {}, 2, &mf);
     if (rc == OUTLETS_OK)
-        rc = run_layer(ctx, ctx->cb, true, n_req, static_cast<int>(T), h_low, h_mid, h_high, row_stride, tokens,
+        rc = run_layer(ctx, ctx->cb, mf, true, n_req, static_cast<int>(T), h_low, h_mid, h_high, row_stride, tokens,
                        z_out, hdraft_out, st);
     if (rc) {
         std::string msg = g_err;
@@ -1014,14 +1013,13 @@ int outlets_predict_step_noalloc(outlets_ctx* ctx, int32_t n_req, const int32_t*
 // per-slot running sums.
 
 // Stage int32 metadata through the pinned double buffer into probe_meta (the
-// metadata kernel in copy-only mode: no copy-engine transfer to wait on).
+// a copy kernel: no copy-engine transfer to wait on).
 int upload_probe_meta(outlets_ctx* c, const std::vector<int32_t>& v, hipStream_t st) {
     if (static_cast<int64_t>(v.size()) > c->cb.meta_cap) return fail(OUTLETS_ERR_INVALID_ARG, "call metadata exceeds capacity");
     const int s = c->stage;
     if (c->ev_used[s]) HIP_TRY(hipEventSynchronize(c->ev[s]), "hipEventSynchronize");
     std::memcpy(c->h_stage[s], v.data(), sizeof(int32_t) * v.size());
-    launch_meta_fetch(c->h_stage[s], static_cast<int>(v.size()), 0, 0, c->probe_meta, nullptr, nullptr, nullptr,
-                      nullptr, st);
+    launch_copy_meta(c->h_stage[s], static_cast<int>(v.size()), c->probe_meta, st);
     HIP_TRY(hipEventRecord(c->ev[s], st), "hipEventRecord");
     c->ev_used[s] = true;
     c->stage ^= 1;

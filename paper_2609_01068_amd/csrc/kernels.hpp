@@ -101,16 +101,25 @@ int gemm_device_cus();   // compute units of the current device
 bool gemm_qkv_rope_fusable(int act_fmt, int w_fmt, int n_q, int n_kv, int hd, int N);
 
 // ---------------------------------------------------------------- elementwise / rows
-// A call's metadata block from pinned host-coherent memory (`host_meta`,
-// `count` int32: req_off[n + 1] | req_slot[n] | req_start[n] | n_pairs
-// (index, page) pairs | the rest) into d_meta; applies the pairs to
-// page_table and writes tok_slot[T] (slot of each token), tok_pos[T]
-// (req_start + index within the request) and last_idx[n] (row of each
-// request's newest token).  With n_req = n_pairs = 0 it only copies (the
-// other pointers may then be null).  The host must not rewrite host_meta
-// until the kernel has run.
-void launch_meta_fetch(const int32_t* host_meta, int count, int n_req, int n_pairs, int32_t* d_meta,
-                       int32_t* page_table, int32_t* tok_slot, int32_t* tok_pos, int32_t* last_idx, hipStream_t st);
+// A call's metadata block from pinned host-coherent memory (`host`, `count`
+// int32: req_off[n + 1] | req_slot[n] | req_start[n] | n_pairs (index, page)
+// pairs | the rest) into d_meta, applying the pairs to page_table and writing
+// tok_slot[T] (slot of each token), tok_pos[T] (req_start + index within the
+// request) and last_idx[n] (row of each request's newest token): work that
+// launch_rmsnorm and launch_rmsnorm_sum do in `blocks` blocks beside their
+// rows (0: none).  The host must not rewrite `host` until the kernel has run.
+struct MetaFetch {
+    const int32_t* host;
+    int count, n_req, n_pairs, blocks;
+    int32_t* d_meta;
+    int32_t* page_table;
+    int32_t* tok_slot;
+    int32_t* tok_pos;
+    int32_t* last_idx;
+};
+int meta_fetch_blocks(int count, int n_req);
+// Only the copy of `count` int32 from pinned host-coherent memory.
+void launch_copy_meta(const int32_t* host_meta, int count, int32_t* d_meta, hipStream_t st);
 
 // Row x[r] of a split-K GEMM's output: the S partial planes summed in split
 // order, plus resid[r] when resid is set (the fp32 residual the GEMM's
@@ -132,11 +141,11 @@ bool rowsum_supported(int d);
 // (either output may be null; y2 is an fp32 copy and may alias x).
 void launch_rmsnorm(int act_fmt, int gamma_fmt, int rows, int d, const float* x, int64_t ldx,
                     const void* gamma, float eps, void* y, int64_t ldy, float* y2,
-                    int64_t ldy2, hipStream_t st);
+                    int64_t ldy2, hipStream_t st, const MetaFetch& mf = MetaFetch{});
 
 // launch_rmsnorm of the rows a RowSum forms (rowsum_supported(d) must hold).
 void launch_rmsnorm_sum(int act_fmt, int gamma_fmt, int rows, int d, const RowSum& rs, const void* gamma,
-                        float eps, void* y, int64_t ldy, hipStream_t st);
+                        float eps, void* y, int64_t ldy, hipStream_t st, const MetaFetch& mf = MetaFetch{});
 
 // EAGLE-3 input embeddings: y[r] = RMSNorm(embed[tok[r]]) * gamma for `rows`
 // token ids; embed [vocab, d] and y in act format, gamma in gamma_fmt.  Ids

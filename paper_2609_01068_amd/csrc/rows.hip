@@ -14,39 +14,50 @@ namespace {
 // memory, copied into device memory together with the two things later
 // kernels need from it first: the page-table updates (the (index, page)
 // pairs after req_off | req_slot | req_start) and the per-token slot and
-// position arrays.  One launch instead of a copy-engine transfer, whose
-// completion the compute queue would wait on, and two kernels.  `host` is
-// read with vector loads (it is not restrict-qualified), so nothing of it is
-// kept in the scalar cache.
-__global__ void __launch_bounds__(256)
-meta_fetch_kernel(const int32_t* host, int count, int n_req, int n_pairs, int32_t* __restrict__ d_meta,
-                  int32_t* __restrict__ page_table, int32_t* __restrict__ tok_slot, int32_t* __restrict__ tok_pos,
-                  int32_t* __restrict__ last_idx) {
-    const int tid = blockIdx.x * blockDim.x + threadIdx.x, nth = gridDim.x * blockDim.x;
-    const int n4 = count / 4;
-    const uint4* h4 = reinterpret_cast<const uint4*>(host);
-    uint4* d4 = reinterpret_cast<uint4*>(d_meta);
-    for (int i = tid; i < n4; i += nth) d4[i] = h4[i];
-    for (int i = 4 * n4 + tid; i < count; i += nth) d_meta[i] = host[i];
-    const int32_t* pairs = host + 3 * n_req + 1;
-    for (int i = tid; i < n_pairs; i += nth) page_table[pairs[2 * i]] = pairs[2 * i + 1];
-    for (int r = blockIdx.x; r < n_req; r += gridDim.x) {
-        const int b = host[r], e = host[r + 1], slot = host[n_req + 1 + r], start = host[2 * n_req + 1 + r];
-        for (int t = b + threadIdx.x; t < e; t += blockDim.x) {
-            tok_slot[t] = slot;
-            tok_pos[t] = start + (t - b);
+// position arrays.  Done by mf.blocks extra blocks of the layer's first norm,
+// whose rows do not need it (nor does the GEMM before): a copy-engine transfer
+// would have to be waited on by the compute queue, and a kernel of its own
+// waited for the host link with the chip idle (one request with a 777-token
+// prompt, prefill and 8 steps at the 8B widths: 1,878 us a kernel of its own,
+// 1,833 beside the norm; 512-request step 1,831 / 1,804).  `host` is read with
+// vector loads (it is not restrict-qualified, and the index differs by lane
+// or wave), so nothing of it is kept in the scalar cache.  One wave per
+// request: each wave's reads cross the link again, and a block per request
+// with loads in order made the 512-request step 130 us slower.
+__device__ void meta_fetch_block(const MetaFetch& mf, int block) {
+    const int tid = block * blockDim.x + threadIdx.x, nth = mf.blocks * blockDim.x;
+    const int32_t* host = mf.host;
+    const int n4 = mf.count / 4;
+    for (int i = tid; i < n4; i += nth)
+        reinterpret_cast<uint4*>(mf.d_meta)[i] = reinterpret_cast<const uint4*>(host)[i];
+    for (int i = 4 * n4 + tid; i < mf.count; i += nth) mf.d_meta[i] = host[i];
+    const int32_t* pairs = host + 3 * mf.n_req + 1;
+    for (int i = tid; i < mf.n_pairs; i += nth) mf.page_table[pairs[2 * i]] = pairs[2 * i + 1];
+    const int lane = threadIdx.x % 64;
+    for (int r = tid / 64; r < mf.n_req; r += nth / 64) {
+        const int b = host[r], e = host[r + 1], slot = host[mf.n_req + 1 + r], start = host[2 * mf.n_req + 1 + r];
+        for (int t = b + lane; t < e; t += 64) {
+            mf.tok_slot[t] = slot;
+            mf.tok_pos[t] = start + (t - b);
         }
-        if (threadIdx.x == 0) last_idx[r] = e - 1;
+        if (lane == 0) mf.last_idx[r] = e - 1;
     }
 }
 
-// One 256-thread block per row.
+// Only the copy (the probe's metadata), as above.
+__global__ void __launch_bounds__(256)
+copy_meta_kernel(const int32_t* host, int count, int32_t* __restrict__ d_meta) {
+    for (int i = blockIdx.x * 256 + threadIdx.x; i < count; i += gridDim.x * 256) d_meta[i] = host[i];
+}
+
+// One 256-thread block per row (and mf.blocks more, first, for the metadata).
 template <typename TY, typename TG>
 __global__ void __launch_bounds__(256)
 rmsnorm_kernel(int d, const float* x, int64_t ldx, const TG* gamma, float eps, TY* y,
-               int64_t ldy, float* y2, int64_t ldy2) {
+               int64_t ldy, float* y2, int64_t ldy2, MetaFetch mf) {
     __shared__ float red[4];
-    const int64_t row = blockIdx.x;
+    if (static_cast<int>(blockIdx.x) < mf.blocks) return meta_fetch_block(mf, blockIdx.x);
+    const int64_t row = blockIdx.x - mf.blocks;
     const float* xr = x + row * ldx;
     float ss = 0.f;
     for (int c = threadIdx.x; c < d; c += 256) {
@@ -98,9 +109,10 @@ __device__ __forceinline__ float4 rowsum_load(const RowSum& rs, int64_t row, int
 template <typename TY, typename TG, int V, bool SUM = false, int NT = 256>
 __global__ void __launch_bounds__(NT)
 rmsnorm_vec_kernel(int d, const float* x, int64_t ldx, const TG* gamma, float eps, TY* y,
-                   int64_t ldy, float* y2, int64_t ldy2, RowSum rs = RowSum{}) {
+                   int64_t ldy, float* y2, int64_t ldy2, MetaFetch mf, RowSum rs = RowSum{}) {
     __shared__ float red[NT / 64];
-    const int64_t row = blockIdx.x;
+    if (static_cast<int>(blockIdx.x) < mf.blocks) return meta_fetch_block(mf, blockIdx.x);
+    const int64_t row = blockIdx.x - mf.blocks;
     const int t = threadIdx.x;
     const float4* xr = reinterpret_cast<const float4*>(x + row * ldx);
     float4 v[V];
@@ -647,18 +659,17 @@ __global__ void copy_rows_kernel(int d, const float* src, int64_t lds, T* dst, i
 
 }  // namespace
 
-void launch_meta_fetch(const int32_t* host_meta, int count, int n_req, int n_pairs, int32_t* d_meta,
-                       int32_t* page_table, int32_t* tok_slot, int32_t* tok_pos, int32_t* last_idx, hipStream_t st) {
+int meta_fetch_blocks(int count, int n_req) { return std::max(1, std::max((n_req + 3) / 4, (count / 4 + 255) / 256)); }
+
+void launch_copy_meta(const int32_t* host_meta, int count, int32_t* d_meta, hipStream_t st) {
     if (count <= 0) return;
-    const int blocks = std::max(1, std::max(n_req, (count / 4 + 255) / 256));
-    hipLaunchKernelGGL(meta_fetch_kernel, dim3(blocks), dim3(256), 0, st, host_meta, count, n_req, n_pairs, d_meta,
-                       page_table, tok_slot, tok_pos, last_idx);
+    hipLaunchKernelGGL(copy_meta_kernel, dim3((count + 255) / 256), dim3(256), 0, st, host_meta, count, d_meta);
 }
 
 bool rowsum_supported(int d) { return d == 1024 || d == 2048 || d == 4096 || d == 8192; }
 
 void launch_rmsnorm_sum(int act_fmt, int gamma_fmt, int rows, int d, const RowSum& rs, const void* gamma,
-                        float eps, void* y, int64_t ldy, hipStream_t st) {
+                        float eps, void* y, int64_t ldy, hipStream_t st, const MetaFetch& mf) {
     if (rows <= 0) return;
     // Up to 512 rows (two per CU) a wide block per row (d / 4 threads, at
     // most 1,024) hides the partials' latency better than 256 threads of d /
@@ -667,9 +678,10 @@ void launch_rmsnorm_sum(int act_fmt, int gamma_fmt, int rows, int d, const RowSu
     // 7.7, 130 rows of 8 12.0 / 6.9, 512 rows of 4 10.6 / 10.1; 777 rows of 4
     // narrow 13.4 (6 TB/s).
     const bool wide = rows <= 512;
+    const dim3 grid(rows + mf.blocks);
 #define OUTLETS_NORMS_L(TY, TG, VV, NT)                                                                    \
-    hipLaunchKernelGGL((rmsnorm_vec_kernel<TY, TG, VV, true, NT>), dim3(rows), dim3(NT), 0, st, d, nullptr, 0, \
-                       static_cast<const TG*>(gamma), eps, static_cast<TY*>(y), ldy, nullptr, 0, rs)
+    hipLaunchKernelGGL((rmsnorm_vec_kernel<TY, TG, VV, true, NT>), grid, dim3(NT), 0, st, d, nullptr, 0,   \
+                       static_cast<const TG*>(gamma), eps, static_cast<TY*>(y), ldy, nullptr, 0, mf, rs)
 #define OUTLETS_NORMS_V(TY, TG)                                                                            \
     switch (d / 1024) {                                                                                    \
         case 1: OUTLETS_NORMS_L(TY, TG, 1, 256); break;                                                    \
@@ -686,8 +698,9 @@ void launch_rmsnorm_sum(int act_fmt, int gamma_fmt, int rows, int d, const RowSu
 
 void launch_rmsnorm(int act_fmt, int gamma_fmt, int rows, int d, const float* x, int64_t ldx,
                     const void* gamma, float eps, void* y, int64_t ldy, float* y2,
-                    int64_t ldy2, hipStream_t st) {
+                    int64_t ldy2, hipStream_t st, const MetaFetch& mf) {
     if (rows <= 0) return;
+    const dim3 grid(rows + mf.blocks);
     // vectorised path: d a multiple of 1024 up to 8192, 16-byte aligned rows
     const bool vec = d % 1024 == 0 && d <= 8192 && ldx % 4 == 0 && (!y || ldy % 4 == 0) &&
                      (!y2 || ldy2 % 4 == 0) && reinterpret_cast<uintptr_t>(x) % 16 == 0 &&
@@ -698,14 +711,14 @@ void launch_rmsnorm(int act_fmt, int gamma_fmt, int rows, int d, const float* x,
         const int V = d / 1024;
 #define OUTLETS_NORM_V(TY, TG)                                                                  \
     switch (V) {                                                                                \
-        case 1: hipLaunchKernelGGL((rmsnorm_vec_kernel<TY, TG, 1>), dim3(rows), dim3(256), 0, st, d, x, ldx, \
-                                   static_cast<const TG*>(gamma), eps, static_cast<TY*>(y), ldy, y2, ldy2); break; \
-        case 2: hipLaunchKernelGGL((rmsnorm_vec_kernel<TY, TG, 2>), dim3(rows), dim3(256), 0, st, d, x, ldx, \
-                                   static_cast<const TG*>(gamma), eps, static_cast<TY*>(y), ldy, y2, ldy2); break; \
-        case 4: hipLaunchKernelGGL((rmsnorm_vec_kernel<TY, TG, 4>), dim3(rows), dim3(256), 0, st, d, x, ldx, \
-                                   static_cast<const TG*>(gamma), eps, static_cast<TY*>(y), ldy, y2, ldy2); break; \
-        case 8: hipLaunchKernelGGL((rmsnorm_vec_kernel<TY, TG, 8>), dim3(rows), dim3(256), 0, st, d, x, ldx, \
-                                   static_cast<const TG*>(gamma), eps, static_cast<TY*>(y), ldy, y2, ldy2); break; \
+        case 1: hipLaunchKernelGGL((rmsnorm_vec_kernel<TY, TG, 1>), grid, dim3(256), 0, st, d, x, ldx, \
+                                   static_cast<const TG*>(gamma), eps, static_cast<TY*>(y), ldy, y2, ldy2, mf); break; \
+        case 2: hipLaunchKernelGGL((rmsnorm_vec_kernel<TY, TG, 2>), grid, dim3(256), 0, st, d, x, ldx, \
+                                   static_cast<const TG*>(gamma), eps, static_cast<TY*>(y), ldy, y2, ldy2, mf); break; \
+        case 4: hipLaunchKernelGGL((rmsnorm_vec_kernel<TY, TG, 4>), grid, dim3(256), 0, st, d, x, ldx, \
+                                   static_cast<const TG*>(gamma), eps, static_cast<TY*>(y), ldy, y2, ldy2, mf); break; \
+        case 8: hipLaunchKernelGGL((rmsnorm_vec_kernel<TY, TG, 8>), grid, dim3(256), 0, st, d, x, ldx, \
+                                   static_cast<const TG*>(gamma), eps, static_cast<TY*>(y), ldy, y2, ldy2, mf); break; \
         default: goto scalar;                                                                   \
     }
         if (act_fmt == FMT_F32) { OUTLETS_NORM_V(float, float) }
@@ -716,14 +729,14 @@ void launch_rmsnorm(int act_fmt, int gamma_fmt, int rows, int d, const float* x,
     }
 scalar:
     if (act_fmt == FMT_F32) {
-        hipLaunchKernelGGL((rmsnorm_kernel<float, float>), dim3(rows), dim3(256), 0, st, d, x, ldx,
-                           static_cast<const float*>(gamma), eps, static_cast<float*>(y), ldy, y2, ldy2);
+        hipLaunchKernelGGL((rmsnorm_kernel<float, float>), grid, dim3(256), 0, st, d, x, ldx,
+                           static_cast<const float*>(gamma), eps, static_cast<float*>(y), ldy, y2, ldy2, mf);
     } else if (gamma_fmt == FMT_F32) {
-        hipLaunchKernelGGL((rmsnorm_kernel<bf16_t, float>), dim3(rows), dim3(256), 0, st, d, x, ldx,
-                           static_cast<const float*>(gamma), eps, static_cast<bf16_t*>(y), ldy, y2, ldy2);
+        hipLaunchKernelGGL((rmsnorm_kernel<bf16_t, float>), grid, dim3(256), 0, st, d, x, ldx,
+                           static_cast<const float*>(gamma), eps, static_cast<bf16_t*>(y), ldy, y2, ldy2, mf);
     } else {
-        hipLaunchKernelGGL((rmsnorm_kernel<bf16_t, bf16_t>), dim3(rows), dim3(256), 0, st, d, x, ldx,
-                           static_cast<const bf16_t*>(gamma), eps, static_cast<bf16_t*>(y), ldy, y2, ldy2);
+        hipLaunchKernelGGL((rmsnorm_kernel<bf16_t, bf16_t>), grid, dim3(256), 0, st, d, x, ldx,
+                           static_cast<const bf16_t*>(gamma), eps, static_cast<bf16_t*>(y), ldy, y2, ldy2, mf);
     }
 }
 

@@ -118,3 +118,33 @@ def test_final_norm_pooling_row_groups(lens):
     say(f"case: pooling tiles, {len(lens)} requests of up to {max(lens)} tokens")
     case = make_case(1, lens=lens, shape=reduced_shape(d=1024, n_q=8, n_kv=2, ffn=1024), n_req=len(lens))
     _against_oracle(case, sorted({0, len(lens) // 2, len(lens) - 1}), TOL_HDRAFT["bf16"], TOL_Z["bf16"])
+
+
+@pytest.mark.parametrize("cfg,shape", [(0, dict(d=256, n_q=4, n_kv=2, ffn=256, head_hidden=128)),
+                                       (1, dict(d=2048, n_q=16, n_kv=4, ffn=2688, head_hidden=256))],
+                         ids=["norm", "summing norm"])
+@pytest.mark.parametrize("lens", [[1], [63, 64, 65], [300, 1, 16, 17, 2], [3] * 257], ids=["1", "3", "5", "257"])
+def test_metadata_beside_the_first_norm(cfg, shape, lens):
+    """The metadata block fetched by extra blocks of the first norm: one wave
+    per request (request counts around four and past a block of waves, tokens
+    around a wave), in the prefill and in two steps.  Whole numbers, exact."""
+    from paper_2609_01068_amd import binding as B
+    say(f"case: metadata, cfg {cfg}, {len(lens)} requests of up to {max(lens)} tokens, 2 steps")
+    case = make_case(cfg, lens=lens, shape=reduced_shape(**shape), n_req=len(lens))
+    n, slots = len(lens), list(range(len(lens)))[::-1]
+    pred = make_predictor(case, max_seq_len=max(lens) + 32)
+
+    def check(pos, lens):
+        assert np.array_equal(pred.meta(B.OUTLETS_META_DEV_POSITIONS), pos)
+        assert np.array_equal(pred.meta(B.OUTLETS_META_DEV_CU_SEQLENS), np.concatenate([[0], np.cumsum(lens)]))
+        assert np.array_equal(pred.meta(B.OUTLETS_META_DEV_LAST_IDX), np.cumsum(lens) - 1)
+        assert np.array_equal(pred.meta(B.OUTLETS_META_DEV_TOKEN_SLOT), np.repeat(slots, lens))
+        table = pred.meta(B.OUTLETS_META_PAGE_TABLE)
+        assert np.array_equal(pred.meta(B.OUTLETS_META_DEV_PAGE_TABLE)[table >= 0], table[table >= 0])
+
+    pred.prefill(slots, case.lens, *device_states(case))
+    check(np.concatenate([np.arange(x) for x in lens]), lens)
+    for k in (1, 2):
+        pred.step(slots, *device_states(case, step_inputs(case, k)))
+        check(np.asarray(lens) + k - 1, [1] * n)
+    pred.close()

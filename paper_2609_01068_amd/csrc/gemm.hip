@@ -1551,7 +1551,8 @@ void launch_f32(int M, int N, int K, const GemmA& a, const GemmB& b, const GemmC
 // Up to 64 rows the few-row kernel, where its workgroups (before any K split)
 // fit the CUs in one round: 224 for the d = 4096 gate/up, 192 for q|k|v; the
 // 501-tile draft model head takes 176 us on 64 x 256 tiles and 216 here, a
-// 10,240-row q|k|v|gate of K = 8192 37 and 55.  With bf16 weights the gate/up
+// 10,240-row q|k|v|gate of K = 8192 and 11 rows 41 in K splits of the tiles
+// and 55 here (161 unsplit).  With bf16 weights the gate/up
 // GEMM of more than 16 rows stays on the tiles too.  Measured against 64 x
 // 256 tiles with their reduces (d = 4096 bf16, 16 / 64 rows, us): fused
 // projection 25.0 / 29.3 -> 21.3 / 27.0, QKV 20.6 / 25.9 -> 19.3 / 24.0, O 13.9 /
@@ -1565,7 +1566,10 @@ void launch_f32(int M, int N, int K, const GemmA& a, const GemmB& b, const GemmC
 bool gemm_streams(int w_fmt, int epi, int M, int N, int K) {
     if (w_fmt == FMT_F32 || epi == EPI_PARTIAL_TILE || (int64_t)N * K < 1 << 22) return false;
     if (M > (w_fmt == FMT_BF16 && epi == EPI_SWIGLU ? 16 : 64)) return false;
-    const int rows = (epi == EPI_SWIGLU ? 32 : 16) * stream_waves(w_fmt == FMT_E4M3, epi, N, device_cus());
+    // rows of a workgroup: the narrow one's of stream_waves for every epilogue
+    // but SwiGLU, so that a split call's partials take the kernel that the
+    // split was planned for
+    const int rows = (epi == EPI_SWIGLU ? 32 : 8) * (w_fmt == FMT_E4M3 ? 8 : 4);
     return N / rows <= device_cus();
 }
 

@@ -93,6 +93,18 @@ def test_few_row_gemm_edges(cfg, rows):
     _against_oracle(case, sorted({0, rows // 2, rows - 1}), TOL_HDRAFT[case.fmt], TOL_Z[case.fmt], steps=2)
 
 
+@pytest.mark.parametrize("cfg", [1, 4], ids=["bf16", "e4m3"])
+@pytest.mark.parametrize("rows", [1, 33])
+def test_few_row_gemm_too_wide_for_one_round(cfg, rows):
+    """A gated q|k|v of more rows than the few-row kernel's workgroups cover in
+    one round (10,240 bf16, 18,432 e4m3): K splits of the tiles and their
+    RoPE reduce.  Tolerance: the repository's bounds for bf16 and e4m3."""
+    shape = reduced_shape(d=1024, n_q=64 if cfg == 4 else 32, n_kv=8, ffn=1024)
+    say(f"case: few rows, wide gated QKV, cfg {cfg}, {rows} requests, 1 step")
+    case = make_case(cfg, lens=[1] * rows, shape=shape, n_req=rows, attn_gate=True)
+    _against_oracle(case, sorted({0, rows // 2, rows - 1}), TOL_HDRAFT[case.fmt], TOL_Z[case.fmt])
+
+
 @pytest.mark.parametrize("cfg,lens", [
     (1, [1, 15, 16, 17, 500, 1007]),            # one workgroup per request: up to 64 pages, waves without pages
     (1, [1007, 1023, 30]),                      # the step crosses 64 pages in one request: ranges instead

@@ -1070,107 +1070,145 @@ gemm_stream(int M, int N, int K, GemmA A, GemmB B, GemmC C, int k_per_split) {
     }
 }
 
-// ---------------------------------------------------------------- tail reduce
+// ---------------------------------------------------------------- split-K reduces
+// The reduces stream the partials once (from the last-level cache mostly), so
+// they wait on loads: four columns per thread, and the loads of four splits
+// before the first is added, in split order.  Against one column per thread,
+// one split at a time (us): tile_reduce of 128 tiles x 2 splits 39 -> 20
+// (residual), 29 -> 15 (fp32), of 80 SwiGLU tiles x 3 19 -> 11; splitk_reduce of
+// 777 x 4,096 x 4 splits 19.5 -> 13.6, of 1,081 x 8,192 x 3 50 -> 29; the RoPE
+// reduce, half of whose time is V's 2-byte stores, 15.4 -> 13.6 (512 tokens).
+
+// Four columns of S partials `stride` floats apart, added in split order.
+__device__ __forceinline__ f32x4 sum_splits(const float* p, int64_t stride, int S) {
+    f32x4 v = {0.f, 0.f, 0.f, 0.f};
+    int sp = 0;
+    for (; sp + 4 <= S; sp += 4, p += 4 * stride) {
+        f32x4 x[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) x[q] = *reinterpret_cast<const f32x4*>(p + q * stride);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v += x[q];
+    }
+    for (; sp < S; ++sp, p += stride) v += *reinterpret_cast<const f32x4*>(p);
+    return v;
+}
+
+__device__ __forceinline__ void store_bf16x4(bf16_t* p, const f32x4& v) {
+    *reinterpret_cast<u32x2*>(p) = u32x2{f32_to_bf16(v[0]) | (uint32_t)f32_to_bf16(v[1]) << 16,
+                                         f32_to_bf16(v[2]) | (uint32_t)f32_to_bf16(v[3]) << 16};
+}
+
+// The unsplit GEMM's epilogue for output columns n .. n + 3 of row m; u: the
+// up columns of EPI_SWIGLU.  vec: rows of C and of the residual are 16-byte
+// aligned.
+template <int EPI>
+__device__ __forceinline__ void reduce_store(const GemmC& C, int m, int n, const f32x4& v, const f32x4& u, bool vec) {
+    if constexpr (EPI == EPI_STORE_F32 || EPI == EPI_RESID_F32) {
+        float* c = static_cast<float*>(C.c) + (int64_t)m * C.ldc + n;
+        const float* r = C.resid + (int64_t)m * C.ldr + n;
+        if (vec) {
+            *reinterpret_cast<f32x4*>(c) = EPI == EPI_RESID_F32 ? *reinterpret_cast<const f32x4*>(r) + v : v;
+            return;
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) c[e] = EPI == EPI_RESID_F32 ? r[e] + v[e] : v[e];
+    } else {
+        bf16_t* c = static_cast<bf16_t*>(C.c) + (int64_t)m * C.ldc + n;
+        f32x4 y = v;
+        if constexpr (EPI == EPI_SWIGLU)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) y[e] = silu_f(v[e]) * u[e];
+        if (vec) return store_bf16x4(c, y);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) c[e] = f32_to_bf16(y[e]);
+    }
+}
+
+bool reduce_vec(const GemmC& c) {
+    return c.ldc % 4 == 0 && reinterpret_cast<uintptr_t>(c.c) % 16 == 0 &&
+           (!c.resid || (c.ldr % 4 == 0 && reinterpret_cast<uintptr_t>(c.resid) % 16 == 0));
+}
+
 // The last tiles of a large GEMM (fewer than the CUs) run as S K-splits into
 // per-tile fp32 blocks ws[s][t][256][256], t = pid - pid0; this sums the S
-// blocks of each element in order and applies the epilogue.  One thread per
-// element of a tile row; SwiGLU threads take gate columns only.
-template <int EPI, typename OutT>
+// blocks of each element in order and applies the epilogue.  A block takes
+// four rows of a tile (SwiGLU eight: its threads take gate columns only).
+template <int EPI>
 __global__ void __launch_bounds__(256)
-tile_reduce(int M, int N, int S, int ntail, int pid0, const float* ws, GemmC C) {
-    const int t = blockIdx.x >> 8, rl = blockIdx.x & 255, cl = threadIdx.x;
+tile_reduce(int M, int N, int S, int ntail, int pid0, const float* ws, GemmC C, bool vec) {
+    constexpr int ROWS = EPI == EPI_SWIGLU ? 8 : 4, TPR = 256 / ROWS, BPT = 256 / ROWS;
+    const int t = blockIdx.x / BPT, rl = blockIdx.x % BPT * ROWS + threadIdx.x / TPR, q = threadIdx.x % TPR;
+    const int cl = EPI == EPI_SWIGLU ? (q >> 3) * 64 + (q & 7) * 4 : q * 4;
     const int mt = (M + 255) / 256, nt = N / 256;
     int tm, tn;
     tile_coords(pid0 + t, mt, nt, tm, tn);
-    const int m = tm * 256 + rl, n = tn * 256 + cl;
+    const int m = tm * 256 + rl;
     if (m >= M) return;
-    if (EPI == EPI_SWIGLU && ((n >> 5) & 1)) return;
-    const int64_t e = (int64_t)rl * 256 + cl, blk = (int64_t)ntail * 65536;
-    float v = 0.f, u = 0.f;
-    for (int sp = 0; sp < S; ++sp) {
-        v += ws[sp * blk + (int64_t)t * 65536 + e];
-        if (EPI == EPI_SWIGLU) u += ws[sp * blk + (int64_t)t * 65536 + e + 32];
-    }
-    if (EPI == EPI_STORE_F32) static_cast<float*>(C.c)[(int64_t)m * C.ldc + n] = v;
-    else if (EPI == EPI_STORE_ACT) store_act<OutT>(static_cast<OutT*>(C.c) + (int64_t)m * C.ldc + n, v);
-    else if (EPI == EPI_RESID_F32)
-        static_cast<float*>(C.c)[(int64_t)m * C.ldc + n] = C.resid[(int64_t)m * C.ldr + n] + v;
-    else if (EPI == EPI_SWIGLU) {
-        const int f = ((n >> 5) >> 1) * 32 + (n & 31);
-        store_act<OutT>(static_cast<OutT*>(C.c) + (int64_t)m * C.ldc + f, silu_f(v) * u);
-    }
+    const int64_t blk = (int64_t)ntail * 65536;
+    const float* p = ws + (int64_t)t * 65536 + rl * 256 + cl;
+    const f32x4 v = sum_splits(p, blk, S);
+    const f32x4 u = EPI == EPI_SWIGLU ? sum_splits(p + 32, blk, S) : v;
+    reduce_store<EPI>(C, m, EPI == EPI_SWIGLU ? tn * 128 + q * 4 : tn * 256 + cl, v, u, vec);
 }
 
-// ---------------------------------------------------------------- split-K reduce
 // part[s][m][n] (fp32, logical columns) summed over s in order, then the
-// epilogue of the unsplit GEMM.  One thread per output element.
-template <int EPI, typename OutT>
+// epilogue of the unsplit GEMM; blockIdx.y is the row.
+template <int EPI>
 __global__ void __launch_bounds__(256)
-splitk_reduce(int M, int N, int S, const float* part, GemmC C) {
-    const int nout = (EPI == EPI_SWIGLU) ? N / 2 : N;
-    const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= (int64_t)M * nout) return;
-    const int m = static_cast<int>(idx / nout), n = static_cast<int>(idx % nout);
+splitk_reduce(int M, int N, int S, const float* part, GemmC C, bool vec) {
+    const int n = (blockIdx.x * 256 + threadIdx.x) * 4, m = blockIdx.y;
+    if (n >= (EPI == EPI_SWIGLU ? N / 2 : N)) return;
     const int64_t plane = (int64_t)M * N;
-    if (EPI == EPI_SWIGLU) {
-        // output feature n = gate column (n/32)*64 + n%32, up column +32
-        const int ng = (n >> 5) * 64 + (n & 31);
-        float g = 0.f, u = 0.f;
-        for (int sp = 0; sp < S; ++sp) {
-            g += part[sp * plane + (int64_t)m * N + ng];
-            u += part[sp * plane + (int64_t)m * N + ng + 32];
-        }
-        store_act<OutT>(static_cast<OutT*>(C.c) + (int64_t)m * C.ldc + n, silu_f(g) * u);
-        return;
-    }
-    float v = 0.f;
-    for (int sp = 0; sp < S; ++sp) v += part[sp * plane + (int64_t)m * N + n];
-    if (EPI == EPI_STORE_F32) static_cast<float*>(C.c)[(int64_t)m * C.ldc + n] = v;
-    else if (EPI == EPI_STORE_ACT) store_act<OutT>(static_cast<OutT*>(C.c) + (int64_t)m * C.ldc + n, v);
-    else if (EPI == EPI_RESID_F32)
-        static_cast<float*>(C.c)[(int64_t)m * C.ldc + n] = C.resid[(int64_t)m * C.ldr + n] + v;
+    // SwiGLU: output feature n = gate column (n/32)*64 + n%32, up column +32
+    const float* p = part + (int64_t)m * N + (EPI == EPI_SWIGLU ? (n >> 5) * 64 + (n & 31) : n);
+    const f32x4 v = sum_splits(p, plane, S);
+    const f32x4 u = EPI == EPI_SWIGLU ? sum_splits(p + 32, plane, S) : v;
+    reduce_store<EPI>(C, m, n, v, u, vec);
 }
 
 // Split-K reduce of the QKV GEMM with the EPI_QKV_ROPE epilogue: one thread
-// per (token, 128-wide head, channel pair c, c + 64); the pair is summed over
-// the splits in order, then rotated (q, k) and stored like the epilogue does.
+// per four channel pairs c, c + 64 of a token's 128-wide head (blockIdx.y: the
+// token); the pairs are summed over the splits in order, then rotated (q, k)
+// and stored like the epilogue does.
 __global__ void __launch_bounds__(256)
 splitk_reduce_qkv_rope(int M, int N, int S, const float* part, GemmC C) {
     const RopeKV& R = C.rope;
-    const int heads = N / 128;
-    const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= (int64_t)M * heads * 64) return;
-    const int c = static_cast<int>(idx & 63);
-    const int64_t th = idx >> 6;
-    const int head = static_cast<int>(th % heads), t = static_cast<int>(th / heads);
+    const int i = blockIdx.x * 256 + threadIdx.x, t = blockIdx.y;
+    const int head = i >> 4, c = (i & 15) * 4;
+    if (head >= N / 128) return;
     const int64_t plane = (int64_t)M * N, e = (int64_t)t * N + head * 128 + c;
-    float x1 = 0.f, x2 = 0.f;
-    for (int sp = 0; sp < S; ++sp) {
-        x1 += part[sp * plane + e];
-        x2 += part[sp * plane + e + 64];
-    }
     const int region = head < R.n_q ? 0 : (head < R.n_q + R.n_kv ? 1 : (head < R.n_q + 2 * R.n_kv ? 2 : 3));
+    const int pos = R.tok_pos[t];
+    const int page = R.page_table[(int64_t)R.tok_slot[t] * R.max_pages + (pos >> 4)];
+    const f32x4 x1 = sum_splits(part + e, plane, S), x2 = sum_splits(part + e + 64, plane, S);
     bf16_t* dst = static_cast<bf16_t*>(C.c) + (int64_t)t * C.ldc + head * 128;
     if (region == 3) {
-        dst[c] = f32_to_bf16(x1);
-        dst[c + 64] = f32_to_bf16(x2);
+        store_bf16x4(dst + c, x1);
+        store_bf16x4(dst + c + 64, x2);
         return;
     }
-    const int pos = R.tok_pos[t];
     const int kvh = region == 1 ? head - R.n_q : head - R.n_q - R.n_kv;
-    if (region > 0) {
-        const int page = R.page_table[(int64_t)R.tok_slot[t] * R.max_pages + (pos >> 4)];
-        if (region == 2) {
-            bf16_t* vb = R.vpool + ((int64_t)page * R.n_kv + kvh) * 128 * 16 + (pos & 15);
-            vb[c * 16] = f32_to_bf16(x1);
-            vb[(c + 64) * 16] = f32_to_bf16(x2);
-            return;
+    if (region == 2) {
+        bf16_t* vb = R.vpool + ((int64_t)page * R.n_kv + kvh) * 128 * 16 + (pos & 15);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            vb[(c + q) * 16] = f32_to_bf16(x1[q]);
+            vb[(c + q + 64) * 16] = f32_to_bf16(x2[q]);
         }
-        dst = R.kpool + (((int64_t)page * R.n_kv + kvh) * 16 + (pos & 15)) * 128;
+        return;
     }
-    const float cs = R.cos_t[(int64_t)pos * 64 + c], sn = R.sin_t[(int64_t)pos * 64 + c];
-    dst[c] = f32_to_bf16(x1 * cs - x2 * sn);
-    dst[c + 64] = f32_to_bf16(x2 * cs + x1 * sn);
+    if (region == 1) dst = R.kpool + (((int64_t)page * R.n_kv + kvh) * 16 + (pos & 15)) * 128;
+    const f32x4 cs = *reinterpret_cast<const f32x4*>(R.cos_t + (int64_t)pos * 64 + c);
+    const f32x4 sn = *reinterpret_cast<const f32x4*>(R.sin_t + (int64_t)pos * 64 + c);
+    f32x4 lo, hi;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        lo[q] = x1[q] * cs[q] - x2[q] * sn[q];
+        hi[q] = x2[q] * cs[q] + x1[q] * sn[q];
+    }
+    store_bf16x4(dst + c, lo);
+    store_bf16x4(dst + c + 64, hi);
 }
 
 // ---------------------------------------------------------------- fp32 path
@@ -1513,8 +1551,8 @@ void launch_mfma(int act_fmt, int M, int N, int K, const GemmA& a, const GemmB& 
     GemmC pc{};
     pc.c = ws;
     launch_tiles<EPI_PARTIAL_TILE, E4M3>(M, N, K, a, b, pc, S, T - tail, tail, st);
-    hipLaunchKernelGGL((tile_reduce<EPI, bf16_t>), dim3(tail * 256), dim3(256), 0, st, M, N, S, tail,
-                       T - tail, ws, c);
+    hipLaunchKernelGGL((tile_reduce<EPI>), dim3(tail * (EPI == EPI_SWIGLU ? 32 : 64)), dim3(256), 0, st, M, N, S, tail,
+                       T - tail, ws, c, reduce_vec(c));
 }
 
 template <int EPI>
@@ -1666,16 +1704,15 @@ void gemm_launch(int act_fmt, int w_fmt, int epi, int M, int N, int K, const Gem
         pc.split_stride = (int64_t)M * N;
         gemm_launch(act_fmt, w_fmt, EPI_PARTIAL, M, N, K, a, b, pc, sk, st, nullptr, 0);
         const int nout = (epi == EPI_SWIGLU) ? N / 2 : N;
-        const int64_t total = (int64_t)M * nout;
-        const dim3 grid((unsigned)((total + 255) / 256));
+        const dim3 grid((nout + 1023) / 1024, M);
+        const bool vec = reduce_vec(c);
         switch (epi) {
-            case EPI_STORE_F32: hipLaunchKernelGGL((splitk_reduce<EPI_STORE_F32, bf16_t>), grid, dim3(256), 0, st, M, N, sk, ws, c); break;
-            case EPI_STORE_ACT: hipLaunchKernelGGL((splitk_reduce<EPI_STORE_ACT, bf16_t>), grid, dim3(256), 0, st, M, N, sk, ws, c); break;
-            case EPI_RESID_F32: hipLaunchKernelGGL((splitk_reduce<EPI_RESID_F32, bf16_t>), grid, dim3(256), 0, st, M, N, sk, ws, c); break;
-            case EPI_SWIGLU: hipLaunchKernelGGL((splitk_reduce<EPI_SWIGLU, bf16_t>), grid, dim3(256), 0, st, M, N, sk, ws, c); break;
+            case EPI_STORE_F32: hipLaunchKernelGGL((splitk_reduce<EPI_STORE_F32>), grid, dim3(256), 0, st, M, N, sk, ws, c, vec); break;
+            case EPI_STORE_ACT: hipLaunchKernelGGL((splitk_reduce<EPI_STORE_ACT>), grid, dim3(256), 0, st, M, N, sk, ws, c, vec); break;
+            case EPI_RESID_F32: hipLaunchKernelGGL((splitk_reduce<EPI_RESID_F32>), grid, dim3(256), 0, st, M, N, sk, ws, c, vec); break;
+            case EPI_SWIGLU: hipLaunchKernelGGL((splitk_reduce<EPI_SWIGLU>), grid, dim3(256), 0, st, M, N, sk, ws, c, vec); break;
             case EPI_QKV_ROPE:
-                hipLaunchKernelGGL(splitk_reduce_qkv_rope, dim3((unsigned)(((int64_t)M * (N / 2) + 255) / 256)), dim3(256),
-                                   0, st, M, N, sk, ws, c);
+                hipLaunchKernelGGL(splitk_reduce_qkv_rope, dim3((N / 8 + 255) / 256, M), dim3(256), 0, st, M, N, sk, ws, c);
                 break;
         }
         return;

@@ -24,12 +24,6 @@ namespace outlets {
 
 namespace {
 
-#ifndef OUTLETS_GEMM_SPLITMAP
-#define OUTLETS_GEMM_SPLITMAP 2   // K-split launches dealt split-major over the XCDs (0 = by tile; 1 = small-M splits only)
-#endif
-#ifndef OUTLETS_GEMM_GMFULL
-#define OUTLETS_GEMM_GMFULL 4     // up to this many row tiles, one group holds them all (0 = off)
-#endif
 constexpr int BK = 64;                // K slice
 // LDS is read through vector types: for the runtime's struct types (uint2) the
 // compiler cannot tell the read from a copy in flight and waits for all of them.
@@ -55,11 +49,11 @@ __device__ __forceinline__ float silu_f(float g) { return g * __builtin_amdgcn_r
 // Tile order: pid walks GM row-tiles before moving along N, so A rows and
 // B columns are reused from L2.  GM = 3 for wide outputs (>= 64 column
 // tiles) and 2 otherwise (measured best among 1-16 on the draft layer's
-// shapes); with at most OUTLETS_GEMM_GMFULL row tiles (a decode step's few
+// shapes); with at most four row tiles (a decode step's few
 // hundred rows) all of them, so each weight column tile is wanted by one
 // run of pids, i.e. by one XCD.
 __host__ __device__ __forceinline__ void tile_coords(int pid, int mt, int nt, int& tm, int& tn) {
-    const int GM = (mt >= 1 && mt <= OUTLETS_GEMM_GMFULL) ? mt : (nt >= 64 ? 3 : 2);
+    const int GM = (mt >= 1 && mt <= 4) ? mt : (nt >= 64 ? 3 : 2);
     const int group = pid / (GM * nt);
     const int first = group * GM;
     const int gsize = (mt - first < GM) ? mt - first : GM;
@@ -142,25 +136,18 @@ __device__ __forceinline__ int swz_chunk(int row, int c) {
 // + col0 .. of the tile at m0, n0) with the epilogue EPI.
 template <int EPI, bool E4M3, int BM, int FM, int FN>
 __device__ __forceinline__ void gemm_epilogue(f32x4 (&acc)[FM][FN], int M, const GemmB& B, const GemmC& C, int m0,
-                                              int n0, int row0, int col0, int split, int64_t slot) {
-    constexpr int BN = 256;
+                                              int n0, int row0, int col0, int split) {
     const int lane = threadIdx.x & 63, grp = lane >> 4, l16 = lane & 15;
     // epilogue: lane holds column l16 of each 16x16 block, rows 4 g + q for
     // accumulator element q.  Outputs (and the residual) go through
     // descriptors based at the tile's first row whose size ends at row M:
     // stores to rows past M are dropped by the range check, so there are no
-    // per-element branches, and the offsets are 32-bit.  EPI_PARTIAL_TILE
-    // writes the whole tile to its own 256 x 256 block `slot` of the workspace.
-    constexpr bool F32OUT = EPI == EPI_STORE_F32 || EPI == EPI_RESID_F32 || EPI == EPI_PARTIAL ||
-                            EPI == EPI_PARTIAL_TILE;
+    // per-element branches, and the offsets are 32-bit.
+    constexpr bool F32OUT = EPI == EPI_STORE_F32 || EPI == EPI_RESID_F32 || EPI == EPI_PARTIAL;
     constexpr int OSZ = F32OUT ? 4 : 2;   // activations are bf16
-    const int rows_valid = EPI == EPI_PARTIAL_TILE ? BM : min(BM, M - m0);
-    const int ldc = EPI == EPI_PARTIAL_TILE ? BN : static_cast<int>(C.ldc);   // tile offsets fit 32 bits
-    const int ncol0 = EPI == EPI_PARTIAL_TILE ? n0 : 0;       // column origin of the output block
-    char* cbase =
-        EPI == EPI_PARTIAL_TILE
-            ? static_cast<char*>(C.c) + slot * (BM * BN * 4)
-            : static_cast<char*>(C.c) +
+    const int rows_valid = min(BM, M - m0);
+    const int ldc = static_cast<int>(C.ldc);   // tile offsets fit 32 bits
+    char* cbase = static_cast<char*>(C.c) +
                   ((EPI == EPI_PARTIAL ? (int64_t)split * C.split_stride : 0) + (int64_t)m0 * C.ldc) * OSZ;
     const __amdgpu_buffer_rsrc_t rc = buf_rsrc(cbase, (int64_t)rows_valid * ldc * OSZ);
     const int ldr = static_cast<int>(C.ldr);
@@ -216,9 +203,8 @@ __device__ __forceinline__ void gemm_epilogue(f32x4 (&acc)[FM][FN], int M, const
                 for (int q = 0; q < 4; ++q) {
                     const int row = row0 + i * 16 + 4 * grp + q;
                     const float v = acc[i][j][q] * sc;
-                    if (EPI == EPI_STORE_F32 || EPI == EPI_STORE_ACT || EPI == EPI_PARTIAL ||
-                        EPI == EPI_PARTIAL_TILE) {
-                        put(static_cast<uint32_t>((row * ldc + n - ncol0) * OSZ), v);
+                    if (EPI == EPI_STORE_F32 || EPI == EPI_STORE_ACT || EPI == EPI_PARTIAL) {
+                        put(static_cast<uint32_t>((row * ldc + n) * OSZ), v);
                     } else if (EPI == EPI_RESID_F32) {
                         put(static_cast<uint32_t>((row * ldc + n) * OSZ), rv[jj][i][q] + v);
                     } else if (EPI == EPI_SWIGLU) {
@@ -275,8 +261,7 @@ gemm_mfma_short(int M, int N, int K, GemmA A, GemmB B, GemmC C, int k_per_split,
     // only, and each weight byte is fetched by one XCD (dealt by tile, every
     // XCD would read all of K for its tiles).
     const int mt = (M + BM - 1) / BM, nt = N / BN;
-    constexpr bool SPLIT_MAJOR = OUTLETS_GEMM_SPLITMAP == 2 ? (EPI == EPI_PARTIAL || EPI == EPI_PARTIAL_TILE)
-                                                            : (OUTLETS_GEMM_SPLITMAP == 1 && EPI == EPI_PARTIAL);
+    constexpr bool SPLIT_MAJOR = EPI == EPI_PARTIAL;
     int bx = 0, split = 0;
     if (SPLIT_MAJOR) {
         const int v = xcd_pid(blockIdx.x + blockIdx.y * gridDim.x, gridDim.x * gridDim.y);
@@ -435,8 +420,7 @@ gemm_mfma_short(int M, int N, int K, GemmA A, GemmB B, GemmC C, int k_per_split,
     }
     wait_dma<0>();   // no LDS copy may outlive the workgroup
 
-    gemm_epilogue<EPI, E4M3, BM, FM, FN>(acc, M, B, C, m0, n0, wm * TM, wn * TN, split,
-                                         (int64_t)split * gridDim.x + (tpid - pid0));
+    gemm_epilogue<EPI, E4M3, BM, FM, FN>(acc, M, B, C, m0, n0, wm * TM, wn * TN, split);
 }
 
 // Writes the 8 x 4 accumulator blocks of one wave of gemm_mfma_256x256 (rows row0 ..
@@ -1364,18 +1348,11 @@ gemm_f32_mfma(int M, int N, int K, GemmA A, GemmB B, GemmC C, int k_per_split) {
     }
 }
 
-#ifndef OUTLETS_GEMM_SKINNY
-#define OUTLETS_GEMM_SKINNY 3   // LDS stages of the 64-row kernel (0: off)
-#endif
-#ifndef OUTLETS_GEMM_MID
-#define OUTLETS_GEMM_MID 512    // calls of up to this many rows may use 128-row tiles (0: never)
-#endif
-#ifndef OUTLETS_GEMM_MIDST
-#define OUTLETS_GEMM_MIDST 3    // LDS stages of the 128-row kernel
-#endif
+constexpr int kShortStages = 3;   // LDS stages of the 64- and 128-row kernels
+constexpr int kShortRows = 512;   // calls of up to this many rows may use 128-row tiles
 
 // Row-tile height for M rows, N columns and depth K: 64 up to 64 rows; 128 up
-// to OUTLETS_GEMM_MID rows when that takes no more rounds over the CUs than
+// to kShortRows rows when that takes no more rounds over the CUs than
 // 256-row tiles (measured at M = 256 and 512: 8-17% faster for N = 4096 and
 // 6,144, and for gate/up at M = 256; at M = 512 gate/up needs two rounds of
 // 128-row tiles and is 25% slower); else 256.  Long K favours the 256-row
@@ -1391,15 +1368,15 @@ int device_cus();
 
 int gemm_bm(int w_fmt, int M, int N, int K, int epi, bool paired) {
     if (epi == EPI_QKV_ROPE || epi == EPI_PARTIAL_TILE) return 256;
-    if (OUTLETS_GEMM_SKINNY > 0 && M <= 64) return 64;
+    if (M <= 64) return 64;
     // explicit K splits of a narrow output up to 1,024 rows (the length
     // head's 2n hi/lo rows x H1 columns): 128-row tiles give twice the
     // workgroups of 256-row ones, which left half the CUs idle (measured at
     // 1,024 x 1,024 with 8 splits: head GEMM + finish 41.5 -> 36.6 us)
-    if (OUTLETS_GEMM_MID > 0 && epi == EPI_PARTIAL && M <= 2 * OUTLETS_GEMM_MID && N <= 1024) return 128;
+    if (epi == EPI_PARTIAL && M <= 2 * kShortRows && N <= 1024) return 128;
     if (!paired && epi != EPI_SWIGLU && N >= 4096 && (w_fmt == FMT_E4M3 ? M > 128 && K >= 8192 : M > 256 && K > 8192))
         return 256;
-    if (OUTLETS_GEMM_MID > 0 && M <= OUTLETS_GEMM_MID) {
+    if (M <= kShortRows) {
         const int W = device_cus(), nt = N / 256;
         if ((((M + 127) / 128) * nt + W - 1) / W <= (((M + 255) / 256) * nt + W - 1) / W) return 128;
     }
@@ -1451,16 +1428,16 @@ void launch_tiles(int M, int N, int K, const GemmA& a, const GemmB& b, const Gem
     const int bm = gemm_bm(E4M3 ? FMT_E4M3 : FMT_BF16, M, N, K, EPI, b.paired != 0);
     // At most 64 rows: 64 x 256 tiles on 4 waves of 64 x 64, with more K
     // slices in flight (the weight stream is what such calls wait on)
-    if constexpr (EPI != EPI_QKV_ROPE && EPI != EPI_PARTIAL_TILE && OUTLETS_GEMM_SKINNY > 0) {
+    if constexpr (EPI != EPI_QKV_ROPE && EPI != EPI_PARTIAL_TILE) {
         if (bm == 64) {
-            hipLaunchKernelGGL((gemm_mfma_short<EPI, E4M3, 1, OUTLETS_GEMM_SKINNY>),
+            hipLaunchKernelGGL((gemm_mfma_short<EPI, E4M3, 1, kShortStages>),
                                dim3(ntiles, splits), dim3(256), 0, st, M, N, K, a, b, c, kps, pid0);
             return;
         }
     }
-    if constexpr (EPI != EPI_QKV_ROPE && EPI != EPI_PARTIAL_TILE && OUTLETS_GEMM_MID > 0) {
+    if constexpr (EPI != EPI_QKV_ROPE && EPI != EPI_PARTIAL_TILE) {
         if (bm == 128) {
-            hipLaunchKernelGGL((gemm_mfma_short<EPI, E4M3, 2, OUTLETS_GEMM_MIDST>),
+            hipLaunchKernelGGL((gemm_mfma_short<EPI, E4M3, 2, kShortStages>),
                                dim3(ntiles, splits), dim3(512), 0, st, M, N, K, a, b, c, kps, pid0);
             return;
         }

@@ -421,7 +421,10 @@ int outlets_varlen_meta(int32_t n_req, const int32_t* lens, int32_t* cu_out,
  * units.  The pages, requests in order, are cut into n_lanes contiguous
  * ranges whose lengths differ by at most one page (one wave per range and
  * KV head); a range's part in one request is a segment (one partial softmax
- * record), walked in pieces of at most 64 pages.  Outputs (host):
+ * record), walked in pieces of at most 64 pages.  Steps of short caches (up
+ * to 64 pages with at most two workgroups per compute unit, or up to 8 pages
+ * with at most six) run one workgroup per request and KV head without a
+ * plan; this function gives the plan of the other steps.  Outputs (host):
  *   counts[3] = n_pieces, n_segs, n_lanes (always written);
  *   work [4 n_pieces] = (request, first page, end page, segment) per piece;
  *   cu_segs [n_req + 1] = first segment of each request (segments of a

@@ -2,8 +2,10 @@
 //
 // bf16 / e4m3-weight path: v_mfma_f32_16x16x32_bf16 blocks (measured 2-6%
 // faster than the same tiling on 32x32x16 blocks) on 256 x 256 x 64 tiles
-// for large calls (gemm_mfma_256x256) and on 64 or 128 x 256 tiles for calls
-// with few rows (gemm_mfma_short).  K slices move global -> LDS by DMA
+// for large calls (gemm_mfma_256x256) and on 64 or 128 x 256 tiles for
+// smaller ones (gemm_mfma_short); up to 64 rows, where the weights are the
+// whole cost, mostly straight from memory into the multiplies (gemm_stream).
+// The tiles' K slices move global -> LDS by DMA
 // (buffer_load_dwordx4 ... lds), so no registers stage them.  16-byte LDS
 // chunks are XOR-swizzled per row (the swizzle is applied to the DMA source
 // addresses, since each lane's LDS slot is fixed), making fragment reads

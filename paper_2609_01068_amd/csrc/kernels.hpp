@@ -90,8 +90,8 @@ int gemm_launch_partials(int act_fmt, int w_fmt, int epi, int M, int N, int K, c
 // (0 when it splits nothing); a call given exactly these bytes takes the
 // same plan as with ws_bytes.
 size_t gemm_workspace_bytes(int w_fmt, int epi, int M, int N, int K, size_t ws_bytes);
-// Whether a call runs on the few-row kernel, which needs no K split to fill
-// the chip (and no workspace).
+// Whether a call runs on the few-row kernel, which needs fewer K splits than
+// the tiles to fill the chip.
 bool gemm_streams(int w_fmt, int epi, int M, int N, int K);
 int gemm_device_cus();   // compute units of the current device
 // Whether gemm_launch takes EPI_QKV_ROPE for this layout (bf16 activations,

@@ -944,7 +944,11 @@ gemm_stream(int M, int N, int K, GemmA A, GemmB B, GemmC C, int k_per_split) {
     };
     if (ns > 0) {
         u32x4 w[P][RB][WL];
+        // wait_dma counts the weight loads issued after a chunk's copies: no
+        // load may move up over them (the copies write LDS, so nothing else
+        // holds the loads back)
         copy_a(0);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int u = 0; u < P; ++u) load(0, u, w[u]);
         // One chunk; FULL: every slice exists (no branches, so the compiler
@@ -956,6 +960,7 @@ gemm_stream(int M, int N, int K, GemmA A, GemmB B, GemmC C, int k_per_split) {
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // chunk c - 1's reads have returned
             barrier_no_fence();
             copy_a(c + 1);                  // (past the end: into the buffer nobody reads again)
+            __builtin_amdgcn_sched_barrier(0);   // loads stay behind the copies
 #pragma unroll
             for (int u = 0; u < P; ++u) {
                 if (FULL || c * (P * KW) + local(u) < ns) multiply(c, u, w[u]);

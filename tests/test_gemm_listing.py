@@ -1,0 +1,58 @@
+"""What the compiled GEMM kernels have to hold, read from the compiler's listing.
+
+The few-row kernel waits for a chunk's activation copies (buffer_load ... lds) by
+counting the weight loads issued after them, so in every block of its code the
+copies have to come first.  Other instruction schedulers of the same compiler
+take other orders wherever the source leaves them free; the source has to fix
+this one for all of them.
+"""
+import concurrent.futures as cf
+import os
+import re
+import subprocess
+
+import pytest
+
+from paper_2609_01068_amd import build
+
+SCHEDULERS = {"default": [], "iterative ILP": ["-mllvm", "-misched=gcn-iterative-ilp"],
+              "no load clusters": ["-mllvm", "-misched-cluster=false"]}
+
+
+@pytest.fixture(scope="module")
+def listings(tmp_path_factory):
+    folder = tmp_path_factory.mktemp("gemm")
+
+    def compile_one(item):
+        name, options = item
+        out = str(folder / (name.replace(" ", "_") + ".s"))
+        cmd = [build.hipcc()] + build._flags(False) + options + [
+            "--cuda-device-only", "-S", os.path.join(build.CSRC, "gemm.hip"), "-o", out]
+        subprocess.run(cmd, check=True, capture_output=True, text=True)
+        with open(out) as f:
+            return name, f.read()
+
+    with cf.ThreadPoolExecutor(len(SCHEDULERS)) as ex:
+        return dict(ex.map(compile_one, SCHEDULERS.items()))
+
+
+@pytest.mark.parametrize("scheduler", SCHEDULERS)
+def test_weight_loads_stay_behind_the_copies(listings, scheduler):
+    kernels = re.findall(r"^(_ZN7outlets\S*gemm_stream\S*):[^\n]*\n(.*?)\.end_amdhsa_kernel", listings[scheduler],
+                         re.M | re.S)
+    assert kernels
+    wrong = []
+    for name, body in kernels:
+        copies = loads = early = 0
+        for line in body.split("\n"):
+            if re.search(r"s_barrier|^\.LBB|s_cbranch|s_branch", line):
+                loads = 0
+            elif re.search(r"(global|flat)_load_dwordx4", line):
+                loads += 1
+            elif re.search(r"buffer_load_dwordx4.* lds", line):
+                copies += 1
+                early += loads > 0
+        assert copies, name
+        if early:
+            wrong.append(name)
+    assert not wrong, f"{len(wrong)} of {len(kernels)} kernels load weights before a copy"

@@ -1394,11 +1394,14 @@ int gemm_bm(int w_fmt, int M, int N, int K, int epi, bool paired) {
 // activations are then read from L2 by a quarter of the workgroups that 16
 // rows each would take; 8 for e4m3, where they are twice the weights' bytes.
 // The RoPE epilogue takes half, so that q|k|v still gives enough workgroups
-// without a split; so does a K split that would leave CUs idle (the length
-// head).
+// without a split; so does a K split that leaves half the CUs idle (the
+// length head).  One that fills more keeps the full width: half of it means
+// more workgroups than CUs in a second, ragged round (three splits of an N =
+// 5,120, K = 15,360 bf16 GEMM, 64 rows, 480 / 240 workgroups: 50 / 41 us; a
+// step of that layer 296 / 273, of d = 3,072 160 / 145).
 int stream_waves(bool e4m3, int epi, int N, int splits) {
     const int nw = e4m3 ? 8 : 4;
-    if (epi == EPI_QKV_ROPE || (epi == EPI_PARTIAL && N / (16 * nw) * splits < device_cus())) return nw / 2;
+    if (epi == EPI_QKV_ROPE || (epi == EPI_PARTIAL && 2 * (N / (16 * nw)) * splits <= device_cus())) return nw / 2;
     return nw;
 }
 
@@ -1575,7 +1578,11 @@ void launch_f32(int M, int N, int K, const GemmA& a, const GemmB& b, const GemmC
 // 501-tile draft model head takes 176 us on 64 x 256 tiles and 216 here, a
 // 10,240-row q|k|v|gate of K = 8192 and 11 rows 41 in K splits of the tiles
 // and 55 here (161 unsplit).  With bf16 weights the gate/up
-// GEMM of more than 16 rows stays on the tiles too.  Measured against 64 x
+// GEMM of more than 16 rows stays on the tiles too, and so does a matrix of
+// more than 64M weights from 33 rows: the tiles stream a larger one faster
+// (64 rows, fused projection, tiles / here: N = 4,096, 50M, 28.0 / 26.4 us; N =
+// 5,120, 79M, 33.9 / 41.4; N = 6,144, 113M, 45.8 / 69.5; N = 7,168, 154M, 55.1 /
+// 79.2).  Measured against 64 x
 // 256 tiles with their reduces (d = 4096 bf16, 16 / 64 rows, us): fused
 // projection 25.0 / 29.3 -> 21.3 / 27.0, QKV 20.6 / 25.9 -> 19.3 / 24.0, O 13.9 /
 // 17.8 -> 10.2 / 13.2, down 25.3 / 31.5 -> 23.9 / 31.6, length head 17.1 / 18.3 ->
@@ -1588,11 +1595,16 @@ void launch_f32(int M, int N, int K, const GemmA& a, const GemmB& b, const GemmC
 bool gemm_streams(int w_fmt, int epi, int M, int N, int K) {
     if (w_fmt == FMT_F32 || epi == EPI_PARTIAL_TILE || (int64_t)N * K < 1 << 22) return false;
     if (M > (w_fmt == FMT_BF16 && epi == EPI_SWIGLU ? 16 : 64)) return false;
+    if (w_fmt == FMT_BF16 && M > 32 && (int64_t)N * K > 1 << 26) return false;
     // rows of a workgroup: the narrow one's of stream_waves for every epilogue
     // but SwiGLU, so that a split call's partials take the kernel that the
     // split was planned for
     const int rows = (epi == EPI_SWIGLU ? 32 : 8) * (w_fmt == FMT_E4M3 ? 8 : 4);
     return N / rows <= device_cus();
+}
+
+int gemm_stream_workgroups(int w_fmt, int epi, int N, int splits) {
+    return N / ((epi == EPI_SWIGLU ? 32 : 16) * stream_waves(w_fmt == FMT_E4M3, epi, N, splits)) * splits;
 }
 
 int gemm_device_cus() { return device_cus(); }
@@ -1602,7 +1614,7 @@ int gemm_splitk_plan(int w_fmt, int epi, int M, int N, int K) {
     const int W = device_cus();
     if (gemm_streams(w_fmt, epi, M, N, K)) {
         // enough splits to give every CU a workgroup, each of at least 1,024 k
-        const int groups = N / ((epi == EPI_SWIGLU ? 32 : 16) * stream_waves(w_fmt == FMT_E4M3, epi, N, 1));
+        const int groups = gemm_stream_workgroups(w_fmt, epi, N, 1);
         return std::max(1, std::min({8, W / std::max(1, groups), K / 1024}));
     }
     const int bm = gemm_bm(w_fmt, M, N, K, epi, false);

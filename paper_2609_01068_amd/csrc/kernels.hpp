@@ -93,6 +93,8 @@ size_t gemm_workspace_bytes(int w_fmt, int epi, int M, int N, int K, size_t ws_b
 // Whether a call runs on the few-row kernel, which needs fewer K splits than
 // the tiles to fill the chip.
 bool gemm_streams(int w_fmt, int epi, int M, int N, int K);
+// Workgroups of a call of `splits` K splits on it.
+int gemm_stream_workgroups(int w_fmt, int epi, int N, int splits);
 int gemm_device_cus();   // compute units of the current device
 // Whether gemm_launch takes EPI_QKV_ROPE for this layout (bf16 activations,
 // head dim 128; N = q|k|v[|gate] columns); otherwise store with

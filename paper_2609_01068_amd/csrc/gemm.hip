@@ -31,6 +31,7 @@ constexpr int BK = 64;                // K slice
 // compiler cannot tell the read from a copy in flight and waits for all of them.
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4_elem __attribute__((ext_vector_type(4), aligned(4)));   // four floats at any float's address
 
 __device__ __forceinline__ int swz(int row, int c) { return row * 8 + (c ^ ((row >> 1) & 7)); }
 
@@ -1218,8 +1219,11 @@ splitk_reduce_qkv_rope(int M, int N, int S, const float* part, GemmC C) {
 // LDS-tiled VALU kernel: a 4-request decode step's projections 47-75 -> ~5 us
 // each, prefill of 164 tokens 507 -> 69 us, of 65,536 tokens 5,220 -> 3,702.
 //
-// VEC: 16-byte loads (rows 16-byte aligned, K and the K segments whole
-// chunks); otherwise element loads with bounds checks.
+// VEC: aligned 16-byte loads (rows 16-byte aligned, K and the K segments whole
+// chunks); otherwise element-aligned 16-byte loads of the whole chunks, and
+// element loads with bounds checks of those that end K or a segment (d =
+// 1,002, prefill of 6,000 / 27,000 tokens, ms: all element loads 7.1 / 39.0, now
+// 3.8 / 21.9; the LDS-tiled VALU kernel 5.7 / 30.7).
 template <int EPI, bool VEC, int WM, int WN, int FM, int FN, int KW, int U>
 __global__ void __launch_bounds__(WM * WN * KW * 64)
 gemm_f32_mfma(int M, int N, int K, GemmA A, GemmB B, GemmC C, int k_per_split) {
@@ -1252,20 +1256,25 @@ gemm_f32_mfma(int M, int N, int K, GemmA A, GemmB B, GemmC C, int k_per_split) {
     auto a_ptr = [&](int s) { return static_cast<const float*>(s == 0 ? A.p[0] : (s == 1 ? A.p[1] : A.p[2])); };
     auto load = [&](int c, float (*av)[4], float (*bv)[FN][4]) {
         const int k = kb + 16 * c + 4 * grp;
-        if constexpr (VEC) {
-            const int s = (kb + 16 * c) / A.kseg;        // a chunk lies in one segment
-            const float* ap = a_ptr(s) + (k - s * A.kseg);
+        const int s0 = (kb + 16 * c) / A.kseg;
+        // a whole chunk of one K segment: 16-byte loads, also where rows are
+        // only element-aligned (VEC: every chunk)
+        if (VEC || (kb + 16 * c + 16 <= ke && kb + 16 * c + 16 <= (s0 + 1) * A.kseg)) {
+            typedef typename std::conditional<VEC, f32x4, f32x4_elem>::type vec;
+            const float* ap = a_ptr(s0) + (k - s0 * A.kseg);
 #pragma unroll
             for (int i = 0; i < FM; ++i) {
-                const float4 v = *reinterpret_cast<const float4*>(ap + arow[i]);
-                av[i][0] = v.x; av[i][1] = v.y; av[i][2] = v.z; av[i][3] = v.w;
+                const f32x4 v = *reinterpret_cast<const vec*>(ap + arow[i]);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) av[i][e] = v[e];
             }
 #pragma unroll
             for (int q = 0; q < D; ++q)
 #pragma unroll
                 for (int j = 0; j < FN; ++j) {
-                    const float4 v = *reinterpret_cast<const float4*>(brow[q][j] + k);
-                    bv[q][j][0] = v.x; bv[q][j][1] = v.y; bv[q][j][2] = v.z; bv[q][j][3] = v.w;
+                    const f32x4 v = *reinterpret_cast<const vec*>(brow[q][j] + k);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) bv[q][j][e] = v[e];
                 }
         } else {
 #pragma unroll

@@ -359,8 +359,8 @@ int outlets_get_buffer(outlets_ctx* ctx, int32_t which, void* dst, int64_t nbyte
 
 /* ------------------------------------------------------------ per-kernel timing */
 enum {
-    OUTLETS_K_META = 0,         /* page-table scatter + token metadata: done inside the first norm's launch,
-                                 * so timed under OUTLETS_K_NORM; this group records no launches */
+    OUTLETS_K_META = 0,         /* page-table scatter + token metadata: a launch of its own while this group
+                                 * is timed; otherwise part of the first norm's (OUTLETS_K_NORM) */
     OUTLETS_K_FUSE_GEMM = 1,    /* Eq. 1 projection */
     OUTLETS_K_NORM = 2,         /* the RMSNorms (and the embedding gather + norm) */
     OUTLETS_K_QKV_GEMM = 3,

@@ -386,9 +386,20 @@ int check_gemms(const outlets_ctx* c) {
     return OUTLETS_OK;
 }
 
+// The current staging buffer may be rewritten once the work queued on st so
+// far (its reader among it) is done; the next call takes the other one.
+hipError_t stage_read(outlets_ctx* c, hipStream_t st) {
+    const hipError_t e = hipEventRecord(c->ev[c->stage], st);
+    if (e != hipSuccess) return e;
+    c->ev_used[c->stage] = true;
+    c->stage ^= 1;
+    return hipSuccess;
+}
+
 // Queue the draft layer + head for `T` tokens of `n` requests whose
-// metadata is staged (mf); the first norm brings it to the device, and no
-// kernel before it reads any.
+// metadata is staged (mf); the first norm brings it to the device unless
+// stage_meta queued a kernel for it (mf.blocks = 0), and no kernel before the
+// norm reads any.
 int run_layer(outlets_ctx* c, const CallBufs& b, const MetaFetch& mf, bool prefill, int n, int T, const void* hl,
               const void* hm, const void* hh, int64_t row_stride, const int32_t* tokens, float* z_out,
               void* hdraft_out, hipStream_t st) {
@@ -424,9 +435,7 @@ int run_layer(outlets_ctx* c, const CallBufs& b, const MetaFetch& mf, bool prefi
                              st, mf);
       else
           launch_rmsnorm(af, c->small_fmt, T, d, b.r_f, d, c->w.gamma_attn, eps, b.a_norm, d, nullptr, 0, st, mf);
-      HIP_TRY(hipEventRecord(c->ev[c->stage], st), "hipEventRecord");   // the staging buffer is free again after this
-      c->ev_used[c->stage] = true;
-      c->stage ^= 1;
+      if (mf.blocks) HIP_TRY(stage_read(c, st), "hipEventRecord");
       if (c->embed_in)
           launch_embed_norm(af, c->small_fmt, T, static_cast<int>(d), c->cfg.vocab, tokens, c->w.embed,
                             c->w.gamma_emb, eps, b.e_norm, d, st); }
@@ -540,11 +549,13 @@ int run_layer(outlets_ctx* c, const CallBufs& b, const MetaFetch& mf, bool prefi
     return OUTLETS_OK;
 }
 
-// Stage req_off | req_slot | req_start | updates in pinned memory, for the layer's first norm to fetch.
+// Stage req_off | req_slot | req_start | updates in pinned memory, for the
+// layer's first norm to fetch, or, while OUTLETS_K_META is timed, for a kernel
+// of its own.
 int stage_meta(outlets_ctx* c, const CallBufs& b, int n, const std::vector<int32_t>& off, const int32_t* slots,
                const std::vector<int32_t>& start, const std::vector<int32_t>& updates,
                const std::vector<int32_t>& work, const std::vector<int32_t>& cu_tiles,
-               const std::vector<int32_t>& lanes, int work_stride, MetaFetch* mf) {
+               const std::vector<int32_t>& lanes, int work_stride, MetaFetch* mf, hipStream_t st) {
     const int64_t count = (n + 1) + 2 * static_cast<int64_t>(n) + static_cast<int64_t>(updates.size()) +
                           static_cast<int64_t>(work.size()) + static_cast<int64_t>(cu_tiles.size()) +
                           static_cast<int64_t>(lanes.size());
@@ -568,6 +579,12 @@ int stage_meta(outlets_ctx* c, const CallBufs& b, int n, const std::vector<int32
     *mf = MetaFetch{h, static_cast<int>(count), n, static_cast<int>(updates.size() / 2),
                     meta_fetch_blocks(static_cast<int>(count), n), b.d_meta, c->page_table, b.tok_slot, b.tok_pos,
                     b.last_idx};
+    if (c->prof_on && ((c->prof_mask >> OUTLETS_K_META) & 1u)) {
+        { KTimer t(c, OUTLETS_K_META, st);
+          launch_meta_fetch(*mf, st); }
+        mf->blocks = 0;
+        HIP_TRY(stage_read(c, st), "hipEventRecord");
+    }
     return OUTLETS_OK;
 }
 
@@ -735,7 +752,7 @@ int predict_step_impl(outlets_ctx* ctx, bool noalloc, int32_t n_req, const int32
     ctx->decode_by_request = by_request;
     NoTiming nt(ctx, noalloc);
     MetaFetch mf{};
-    rc = stage_meta(ctx, *bufs, n_req, off, slots, start, updates, plan.work, plan.cu_segs, plan.lanes, 4, &mf);
+    rc = stage_meta(ctx, *bufs, n_req, off, slots, start, updates, plan.work, plan.cu_segs, plan.lanes, 4, &mf, st);
     if (rc == OUTLETS_OK)
         rc = run_layer(ctx, *bufs, mf, false, n_req, n_req, h_low, h_mid, h_high, row_stride, tokens, z_out,
                        hdraft_out, st);
@@ -978,7 +995,7 @@ int outlets_predict_prefill(outlets_ctx* ctx, int32_t n_req, const int32_t* slot
     std::vector<int32_t> cu_tiles(n_req + 1, 0);
     for (int i = 0; i < n_req; ++i) cu_tiles[i + 1] = cu_tiles[i] + (lens[i] + 31) / 32;
     MetaFetch mf{};
-    rc = stage_meta(ctx, ctx->cb, n_req, off, slots, start, updates, work, cu_tiles, {}, 2, &mf);
+    rc = stage_meta(ctx, ctx->cb, n_req, off, slots, start, updates, work, cu_tiles, {}, 2, &mf, st);
     if (rc == OUTLETS_OK)
         rc = run_layer(ctx, ctx->cb, mf, true, n_req, static_cast<int>(T), h_low, h_mid, h_high, row_stride, tokens,
                        z_out, hdraft_out, st);
@@ -1020,9 +1037,7 @@ int upload_probe_meta(outlets_ctx* c, const std::vector<int32_t>& v, hipStream_t
     if (c->ev_used[s]) HIP_TRY(hipEventSynchronize(c->ev[s]), "hipEventSynchronize");
     std::memcpy(c->h_stage[s], v.data(), sizeof(int32_t) * v.size());
     launch_copy_meta(c->h_stage[s], static_cast<int>(v.size()), c->probe_meta, st);
-    HIP_TRY(hipEventRecord(c->ev[s], st), "hipEventRecord");
-    c->ev_used[s] = true;
-    c->stage ^= 1;
+    HIP_TRY(stage_read(c, st), "hipEventRecord");
     return OUTLETS_OK;
 }
 

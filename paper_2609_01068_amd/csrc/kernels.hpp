@@ -120,6 +120,8 @@ struct MetaFetch {
     int32_t* last_idx;
 };
 int meta_fetch_blocks(int count, int n_req);
+// The same work in a launch of its own (mf.blocks blocks), where it is timed.
+void launch_meta_fetch(const MetaFetch& mf, hipStream_t st);
 // Only the copy of `count` int32 from pinned host-coherent memory.
 void launch_copy_meta(const int32_t* host_meta, int count, int32_t* d_meta, hipStream_t st);
 

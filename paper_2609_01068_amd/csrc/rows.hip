@@ -44,6 +44,9 @@ __device__ void meta_fetch_block(const MetaFetch& mf, int block) {
     }
 }
 
+__global__ void __launch_bounds__(256)
+meta_fetch_kernel(MetaFetch mf) { meta_fetch_block(mf, blockIdx.x); }
+
 // Only the copy (the probe's metadata), as above.
 __global__ void __launch_bounds__(256)
 copy_meta_kernel(const int32_t* host, int count, int32_t* __restrict__ d_meta) {
@@ -660,6 +663,10 @@ __global__ void copy_rows_kernel(int d, const float* src, int64_t lds, T* dst, i
 }  // namespace
 
 int meta_fetch_blocks(int count, int n_req) { return std::max(1, std::max((n_req + 3) / 4, (count / 4 + 255) / 256)); }
+
+void launch_meta_fetch(const MetaFetch& mf, hipStream_t st) {
+    hipLaunchKernelGGL(meta_fetch_kernel, dim3(mf.blocks), dim3(256), 0, st, mf);
+}
 
 void launch_copy_meta(const int32_t* host_meta, int count, int32_t* d_meta, hipStream_t st) {
     if (count <= 0) return;

@@ -160,3 +160,32 @@ def test_metadata_beside_the_first_norm(cfg, shape, lens):
         pred.step(slots, *device_states(case, step_inputs(case, k)))
         check(np.asarray(lens) + k - 1, [1] * n)
     pred.close()
+
+
+@pytest.mark.parametrize("cfg,shape", [(0, dict(d=256, n_q=4, n_kv=2, ffn=256, head_hidden=128)),
+                                       (1, dict(d=2048, n_q=16, n_kv=4, ffn=2688, head_hidden=256))],
+                         ids=["fp32", "bf16"])
+@pytest.mark.parametrize("groups", [["META"], None], ids=["only metadata", "all groups"])
+def test_metadata_group_is_timed(cfg, shape, groups):
+    """Each call records one launch of the metadata group while it is timed,
+    and gives the same results, bit for bit, as without timing."""
+    lens = [33, 1, 16, 64, 17]
+    say(f"case: metadata timing, cfg {cfg}, groups {groups}, {len(lens)} requests, 3 steps")
+    case = make_case(cfg, lens=lens, shape=reduced_shape(**shape), n_req=len(lens))
+    slots = list(range(len(lens)))
+    runs = []
+    for timed in (False, True):
+        pred = make_predictor(case)
+        if timed:
+            pred.profile(True, groups=groups)
+        out = list(pred.prefill(slots, case.lens, *device_states(case), want_hdraft=True))
+        for k in (1, 2, 3):
+            out += pred.step(slots, *device_states(case, step_inputs(case, k)), want_hdraft=True)
+        runs.append([tensor_to_f64(x) for x in out])
+        if timed:
+            for call, n in (("prefill", 1), ("step", 3)):
+                ms, launches = pred.profile_read(call)["META"]
+                assert launches == n and ms > 0.0, call
+        pred.close()
+    for a, b in zip(*runs):
+        assert np.array_equal(a, b)

@@ -67,3 +67,17 @@ def test_unaligned_fp32_rows_use_wide_loads(listings):
     assert kernels
     for name, body in kernels:
         assert "global_load_dwordx4" in body, name
+
+
+def _epilogues(listing, kernel):
+    kernels = re.findall(r"^(_ZN7outlets\S*%s\S*):[^\n]*\n(.*?)\.end_amdhsa_kernel" % kernel, listing, re.M | re.S)
+    assert kernels
+    return [(name, body[body.rfind("v_mfma"):] if "v_mfma" in body else body) for name, body in kernels]
+
+
+def test_rope_epilogue_reads_the_tables_once_per_tile(listings):
+    """A row's position, slot and page are a chain of dependent loads; read
+    by every lane for each of its 32 rows, they took 4% of a large prefill's
+    q|k|v."""
+    for name, epilogue in _epilogues(listings["default"], "gemm_mfma_256x256ILi6E"):
+        assert len(re.findall(r"global_load_dword\s", epilogue)) <= 8, name

@@ -473,7 +473,11 @@ __device__ __forceinline__ void gemm_epilogue_pairs(f32x4 (&acc)[8][4], int M, c
         if (region == 2) {
             // V pages hold each channel's 16 tokens contiguously: a lane's 4
             // consecutive rows go out as one 8-byte (or two 4-byte) store per
-            // channel when they are consecutive positions on one page
+            // channel when they are consecutive positions on one page.  Other
+            // rows leave two bytes at a time, 32 bytes apart: there lane l
+            // takes channel l of 16, as a lane's own channels (2 l, 2 l + 1)
+            // spread each store over twice the lines (12,288 x 1,024 q|k|v of
+            // 512 decode rows: 66 us, this way 52)
 #pragma unroll
             for (int i = 0; i < FM; ++i) {
                 const int t0 = m0 + row0 + i * 16 + 4 * grp;
@@ -502,11 +506,16 @@ __device__ __forceinline__ void gemm_epilogue_pairs(f32x4 (&acc)[8][4], int M, c
                 } else {
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {
-                        if (t0 + q >= M) continue;
+                        if (t0 + q >= M) continue;         // (the same in all 16 lanes)
                         bf16_t* vb = R.vpool + ((int64_t)page[q] * R.n_kv + kvh) * 128 * 16 + (pos[q] & 15);
 #pragma unroll
-                        for (int j = 0; j < 4; ++j)
-                            vb[(c + (j & 1) + 64 * (j >> 1)) * 16] = f32_to_bf16(acc[i][j][q] * sc[j]);
+                        for (int j = 0; j < 4; ++j) {
+                            // channel 16 (j % 2) + l16 of half j / 2
+                            const int h = j >> 1, ch = 16 * (j & 1) + l16;
+                            const uint32_t two = __shfl(pack(acc[i][2 * h][q] * sc[2 * h], acc[i][2 * h + 1][q] * sc[2 * h + 1]),
+                                                        (lane & 48) + (ch >> 1), 64);
+                            vb[((col0 & 64) / 2 + ch + 64 * h) * 16] = static_cast<bf16_t>(two >> (16 * (ch & 1)));
+                        }
                     }
                 }
             }
@@ -1195,11 +1204,23 @@ splitk_reduce_qkv_rope(int M, int N, int S, const float* part, GemmC C) {
     }
     const int kvh = region == 1 ? head - R.n_q : head - R.n_q - R.n_kv;
     if (region == 2) {
+        // each store takes 16 neighbouring channels on the 16 lanes of the
+        // head, two bytes every 32; a lane's own four channels would put every
+        // store on a line of its own (3,072 x 1,024 q|k|v of 256 / 512 rows with
+        // the GEMM: 22.3 / 29.2 us, this way 21.5 / 27.8)
         bf16_t* vb = R.vpool + ((int64_t)page * R.n_kv + kvh) * 128 * 16 + (pos & 15);
+        const int lane = threadIdx.x & 63, l16 = lane & 15;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            vb[(c + q) * 16] = f32_to_bf16(x1[q]);
-            vb[(c + q + 64) * 16] = f32_to_bf16(x2[q]);
+        for (int h = 0; h < 2; ++h) {
+            const f32x4& x = h ? x2 : x1;
+            const uint32_t lo = f32_to_bf16(x[0]) | (uint32_t)f32_to_bf16(x[1]) << 16;
+            const uint32_t hi = f32_to_bf16(x[2]) | (uint32_t)f32_to_bf16(x[3]) << 16;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int src = (lane & 48) + 4 * q + (l16 >> 2);
+                const uint32_t a = __shfl(lo, src, 64), b = __shfl(hi, src, 64);
+                vb[(64 * h + 16 * q + l16) * 16] = static_cast<bf16_t>((l16 & 2 ? b : a) >> (16 * (l16 & 1)));
+            }
         }
         return;
     }

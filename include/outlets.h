@@ -251,7 +251,9 @@ int outlets_predict_step(outlets_ctx* ctx, int32_t n_req, const int32_t* slots,
  *     head partial sums, token metadata) live in the library's static
  *     scratch array of 256 MiB on each device, not in the context: a step
  *     whose buffers exceed it fails with OUTLETS_ERR_INVALID_ARG and no
- *     state change (8B shape: up to 512 requests fit);
+ *     state change (8B shape: up to 512 requests fit).  Split-K partial sums
+ *     that alone do not fit stay in the workspace the context was created
+ *     with;
  *   - every no-allocation call on one device shares that array and it keeps
  *     the last call's contents: calls that overlap on one device (several
  *     contexts, streams or threads) race;

@@ -734,12 +734,21 @@ int predict_step_impl(outlets_ctx* ctx, bool noalloc, int32_t n_req, const int32
         const int64_t meta_count = (n_req + 1) + 2 * static_cast<int64_t>(n_req) + 2 * new_pages +
                                    static_cast<int64_t>(plan.work.size() + plan.cu_segs.size() + plan.lanes.size());
         const size_t ws = step_splitk_bytes(ctx, n_req);
-        const size_t need = layout_step(ctx, n_req, n_records, meta_count, ws, nullptr, &sb);
+        size_t need = layout_step(ctx, n_req, n_records, meta_count, ws, nullptr, &sb);
+        // A step that fits but for its split-K partials keeps them in the
+        // context's workspace (never larger than that, see step_splitk_bytes):
+        // the plans grow with the kernels, and must not shrink what fits
+        const bool own_ws = need > kScratchBytes;
+        if (own_ws) need = layout_step(ctx, n_req, n_records, meta_count, 0, nullptr, &sb);
         if (need > kScratchBytes)
             return fail(OUTLETS_ERR_INVALID_ARG, "the step needs " + std::to_string(need) +
                                                      " bytes of scratch; the static scratch holds " +
                                                      std::to_string(kScratchBytes));
-        layout_step(ctx, n_req, n_records, meta_count, ws, static_cast<char*>(ctx->scratch), &sb);
+        layout_step(ctx, n_req, n_records, meta_count, own_ws ? 0 : ws, static_cast<char*>(ctx->scratch), &sb);
+        if (own_ws) {
+            sb.splitk_ws = ctx->cb.splitk_ws;
+            sb.splitk_bytes = ctx->cb.splitk_bytes;
+        }
         bufs = &sb;
     }
     if (by_request) plan = DecodePlan{};

@@ -117,3 +117,44 @@ def test_noalloc_step_refusals_leave_state_unchanged():
         kept.step([0], *[x[:1] for x in device_states(make_case(0), step_inputs(make_case(0), 1))], noalloc=True)
     assert e.value.rc == B.OUTLETS_ERR_UNSUPPORTED
     kept.close()
+
+
+def test_noalloc_step_whose_split_k_partials_do_not_fit():
+    """A wide e4m3 layer and 512 requests: 135 MiB of activations and 126 MiB of
+    split-K partials (7 splits of the down GEMM), more than the 256 MiB of
+    scratch together.  Such steps fitted when the plans had fewer splits; the
+    partials stay in the context's workspace, and the bits are those of the
+    ordinary step.  Weights are finite random codes."""
+    import types
+    import torch
+    from paper_2609_01068_amd.predictor import OutletsPredictor
+    d, n_q, n_kv, ffn, h1, n = 9216, 8, 4, 33920, 256, 512
+    say(f"case: e4m3 d={d} ffn={ffn}, {n} requests, no-allocation step with its partials outside the scratch")
+    r = np.random.default_rng(7)
+
+    def big(rows, cols):
+        codes = r.integers(0, 0x38, (rows, cols), dtype=np.uint8) | (r.integers(0, 2, (rows, 1), dtype=np.uint8) << 7)
+        return codes, np.full(rows, 0x3C00, np.uint16)           # row scale 2^-7
+
+    def small(*shape):
+        return (r.integers(0, 2, shape, dtype=np.uint16) << 15) | np.uint16(0x3C00)
+
+    W = dict(w_proj=big(d, 3 * d), w_q=big(n_q * 128, d), w_k=big(n_kv * 128, d), w_v=big(n_kv * 128, d),
+             w_o=big(d, n_q * 128), w_gate=big(ffn, d), w_up=big(ffn, d), w_down=big(d, ffn), gamma_attn=small(d),
+             gamma_mlp=small(d), gamma_final=small(d), head_w1=small(h1, 2 * d), head_b1=small(h1), head_w2=small(h1),
+             head_b2=small(1))
+    shape = types.SimpleNamespace(d=d, n_q=n_q, n_kv=n_kv, head_dim=128, ffn=ffn, head_hidden=h1, rope_theta=1e4,
+                                  rms_eps=1e-5, vocab=0)
+    pred = OutletsPredictor(shape, "e4m3", "bf16", W, max_slots=2 * n, max_seq_len=16, num_pages=2 * n,
+                            max_batch_tokens=n, max_batch_requests=n)
+    g = torch.Generator(device="cuda").manual_seed(1)
+    H = [torch.randn((n, d), generator=g, device="cuda").bfloat16() for _ in range(6)]
+    halves = list(range(n)), list(range(n, 2 * n))
+    for half in halves:
+        pred.prefill(half, [1] * n, *H[:3])
+    for k in range(2):
+        za, ha = pred.step(halves[0], *H[3:], want_hdraft=True)
+        zb, hb = pred.step(halves[1], *H[3:], want_hdraft=True, noalloc=True)
+        assert torch.isfinite(ha.float()).all()
+        assert torch.equal(za, zb) and torch.equal(ha, hb), k
+    pred.close()

@@ -1114,34 +1114,22 @@ __device__ __forceinline__ void store_bf16x4(bf16_t* p, const f32x4& v) {
 }
 
 // The unsplit GEMM's epilogue for output columns n .. n + 3 of row m; u: the
-// up columns of EPI_SWIGLU.  vec: rows of C and of the residual are 16-byte
-// aligned.
+// up columns of EPI_SWIGLU.  Outputs and residuals of split calls are the
+// library's own 256-byte aligned buffers with rows of a multiple of 128
+// elements, so every access is a whole vector.
 template <int EPI>
-__device__ __forceinline__ void reduce_store(const GemmC& C, int m, int n, const f32x4& v, const f32x4& u, bool vec) {
+__device__ __forceinline__ void reduce_store(const GemmC& C, int m, int n, const f32x4& v, const f32x4& u) {
     if constexpr (EPI == EPI_STORE_F32 || EPI == EPI_RESID_F32) {
-        float* c = static_cast<float*>(C.c) + (int64_t)m * C.ldc + n;
-        const float* r = C.resid + (int64_t)m * C.ldr + n;
-        if (vec) {
-            *reinterpret_cast<f32x4*>(c) = EPI == EPI_RESID_F32 ? *reinterpret_cast<const f32x4*>(r) + v : v;
-            return;
-        }
-#pragma unroll
-        for (int e = 0; e < 4; ++e) c[e] = EPI == EPI_RESID_F32 ? r[e] + v[e] : v[e];
+        f32x4 y = v;
+        if constexpr (EPI == EPI_RESID_F32) y = *reinterpret_cast<const f32x4*>(C.resid + (int64_t)m * C.ldr + n) + v;
+        *reinterpret_cast<f32x4*>(static_cast<float*>(C.c) + (int64_t)m * C.ldc + n) = y;
     } else {
-        bf16_t* c = static_cast<bf16_t*>(C.c) + (int64_t)m * C.ldc + n;
         f32x4 y = v;
         if constexpr (EPI == EPI_SWIGLU)
 #pragma unroll
             for (int e = 0; e < 4; ++e) y[e] = silu_f(v[e]) * u[e];
-        if (vec) return store_bf16x4(c, y);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) c[e] = f32_to_bf16(y[e]);
+        store_bf16x4(static_cast<bf16_t*>(C.c) + (int64_t)m * C.ldc + n, y);
     }
-}
-
-bool reduce_vec(const GemmC& c) {
-    return c.ldc % 4 == 0 && reinterpret_cast<uintptr_t>(c.c) % 16 == 0 &&
-           (!c.resid || (c.ldr % 4 == 0 && reinterpret_cast<uintptr_t>(c.resid) % 16 == 0));
 }
 
 // The last tiles of a large GEMM (fewer than the CUs) run as S K-splits into
@@ -1150,7 +1138,7 @@ bool reduce_vec(const GemmC& c) {
 // four rows of a tile (SwiGLU eight: its threads take gate columns only).
 template <int EPI>
 __global__ void __launch_bounds__(256)
-tile_reduce(int M, int N, int S, int ntail, int pid0, const float* ws, GemmC C, bool vec) {
+tile_reduce(int M, int N, int S, int ntail, int pid0, const float* ws, GemmC C) {
     constexpr int ROWS = EPI == EPI_SWIGLU ? 8 : 4, TPR = 256 / ROWS, BPT = 256 / ROWS;
     const int t = blockIdx.x / BPT, rl = blockIdx.x % BPT * ROWS + threadIdx.x / TPR, q = threadIdx.x % TPR;
     const int cl = EPI == EPI_SWIGLU ? (q >> 3) * 64 + (q & 7) * 4 : q * 4;
@@ -1163,14 +1151,14 @@ tile_reduce(int M, int N, int S, int ntail, int pid0, const float* ws, GemmC C, 
     const float* p = ws + (int64_t)t * 65536 + rl * 256 + cl;
     const f32x4 v = sum_splits(p, blk, S);
     const f32x4 u = EPI == EPI_SWIGLU ? sum_splits(p + 32, blk, S) : v;
-    reduce_store<EPI>(C, m, EPI == EPI_SWIGLU ? tn * 128 + q * 4 : tn * 256 + cl, v, u, vec);
+    reduce_store<EPI>(C, m, EPI == EPI_SWIGLU ? tn * 128 + q * 4 : tn * 256 + cl, v, u);
 }
 
 // part[s][m][n] (fp32, logical columns) summed over s in order, then the
 // epilogue of the unsplit GEMM; blockIdx.y is the row.
 template <int EPI>
 __global__ void __launch_bounds__(256)
-splitk_reduce(int M, int N, int S, const float* part, GemmC C, bool vec) {
+splitk_reduce(int M, int N, int S, const float* part, GemmC C) {
     const int n = (blockIdx.x * 256 + threadIdx.x) * 4, m = blockIdx.y;
     if (n >= (EPI == EPI_SWIGLU ? N / 2 : N)) return;
     const int64_t plane = (int64_t)M * N;
@@ -1178,7 +1166,7 @@ splitk_reduce(int M, int N, int S, const float* part, GemmC C, bool vec) {
     const float* p = part + (int64_t)m * N + (EPI == EPI_SWIGLU ? (n >> 5) * 64 + (n & 31) : n);
     const f32x4 v = sum_splits(p, plane, S);
     const f32x4 u = EPI == EPI_SWIGLU ? sum_splits(p + 32, plane, S) : v;
-    reduce_store<EPI>(C, m, n, v, u, vec);
+    reduce_store<EPI>(C, m, n, v, u);
 }
 
 // Split-K reduce of the QKV GEMM with the EPI_QKV_ROPE epilogue: one thread
@@ -1582,7 +1570,7 @@ void launch_mfma(int act_fmt, int M, int N, int K, const GemmA& a, const GemmB& 
     pc.c = ws;
     launch_tiles<EPI_PARTIAL_TILE, E4M3>(M, N, K, a, b, pc, S, T - tail, tail, st);
     hipLaunchKernelGGL((tile_reduce<EPI>), dim3(tail * (EPI == EPI_SWIGLU ? 32 : 64)), dim3(256), 0, st, M, N, S, tail,
-                       T - tail, ws, c, reduce_vec(c));
+                       T - tail, ws, c);
 }
 
 template <int EPI>
@@ -1744,12 +1732,11 @@ void gemm_launch(int act_fmt, int w_fmt, int epi, int M, int N, int K, const Gem
         gemm_launch(act_fmt, w_fmt, EPI_PARTIAL, M, N, K, a, b, pc, sk, st, nullptr, 0);
         const int nout = (epi == EPI_SWIGLU) ? N / 2 : N;
         const dim3 grid((nout + 1023) / 1024, M);
-        const bool vec = reduce_vec(c);
         switch (epi) {
-            case EPI_STORE_F32: hipLaunchKernelGGL((splitk_reduce<EPI_STORE_F32>), grid, dim3(256), 0, st, M, N, sk, ws, c, vec); break;
-            case EPI_STORE_ACT: hipLaunchKernelGGL((splitk_reduce<EPI_STORE_ACT>), grid, dim3(256), 0, st, M, N, sk, ws, c, vec); break;
-            case EPI_RESID_F32: hipLaunchKernelGGL((splitk_reduce<EPI_RESID_F32>), grid, dim3(256), 0, st, M, N, sk, ws, c, vec); break;
-            case EPI_SWIGLU: hipLaunchKernelGGL((splitk_reduce<EPI_SWIGLU>), grid, dim3(256), 0, st, M, N, sk, ws, c, vec); break;
+            case EPI_STORE_F32: hipLaunchKernelGGL((splitk_reduce<EPI_STORE_F32>), grid, dim3(256), 0, st, M, N, sk, ws, c); break;
+            case EPI_STORE_ACT: hipLaunchKernelGGL((splitk_reduce<EPI_STORE_ACT>), grid, dim3(256), 0, st, M, N, sk, ws, c); break;
+            case EPI_RESID_F32: hipLaunchKernelGGL((splitk_reduce<EPI_RESID_F32>), grid, dim3(256), 0, st, M, N, sk, ws, c); break;
+            case EPI_SWIGLU: hipLaunchKernelGGL((splitk_reduce<EPI_SWIGLU>), grid, dim3(256), 0, st, M, N, sk, ws, c); break;
             case EPI_QKV_ROPE:
                 hipLaunchKernelGGL(splitk_reduce_qkv_rope, dim3((N / 8 + 255) / 256, M), dim3(256), 0, st, M, N, sk, ws, c);
                 break;

@@ -1620,9 +1620,8 @@ void launch_f32(int M, int N, int K, const GemmA& a, const GemmB& b, const GemmC
 // 12.5 / 19.7, the two norms and the pooling (fewer partials to add) 26.0 /
 // 26.7 -> 15.5 / 16.3; gate/up 45.0 / 48.0 -> 46.9 / 60.1; d = 8192 e4m3, 16 / 32
 // rows: fused 72.5 / 75.4 -> 42.6 / 49.1, gate/up 174 / 171 -> 108 / 118, down 70.1 /
-// 72.0 -> 46.7 / 53.8.  Matrices below 4M weights take about 1 us to read, so
-// there is nothing to stream, and on the tiled kernels a request's result
-// does not depend on the rows beside it.
+// 72.0 -> 46.7 / 53.8.  Matrices below 4M weights take about 1 us to read:
+// there is nothing to stream.
 bool gemm_streams(int w_fmt, int epi, int M, int N, int K) {
     if (w_fmt == FMT_F32 || epi == EPI_PARTIAL_TILE || (int64_t)N * K < 1 << 22) return false;
     if (M > (w_fmt == FMT_BF16 && epi == EPI_SWIGLU ? 16 : 64)) return false;

@@ -1,6 +1,7 @@
 """Rules that pick a GEMM kernel and its split, as the library's host code
 computes them (256 compute units where there is no device)."""
 import ctypes as C
+import functools
 
 import pytest
 
@@ -11,8 +12,8 @@ STORE_F32, STORE_ACT, RESID, SWIGLU, PARTIAL, PARTIAL_TILE, QKV_ROPE = range(7)
 WIDTHS = [n for n in range(512, 16385, 256)]
 
 
-@pytest.fixture(scope="module")
-def host():
+@functools.lru_cache(maxsize=None)
+def library_host():
     lib = C.CDLL(build.LIB_PATH)
 
     def function(name, params, result=C.c_int):
@@ -29,6 +30,11 @@ def host():
         workspace_bytes = function("gemm_workspace_bytes", "iiiiim", C.c_size_t)
 
     return Host
+
+
+@pytest.fixture(scope="module")
+def host():
+    return library_host()
 
 
 @pytest.mark.parametrize("fmt", [BF16, E4M3], ids=["bf16", "e4m3"])

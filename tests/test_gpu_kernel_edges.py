@@ -7,8 +7,10 @@ tolerance comes from.
 import numpy as np
 import pytest
 
-from gpu_common import (TOL_HDRAFT, TOL_Z, device_states, make_case, make_predictor, oracle_for, oracle_states, reduced_shape, rel_fro,
+from gpu_common import (TOL_HDRAFT, TOL_VARIANT, TOL_Z, device_states, make_case, make_predictor, oracle_for, oracle_states, reduced_shape, rel_fro,
                         require_gpu, say, step_inputs, tensor_to_f64, z_errors)
+
+from test_gemm_dispatch import BF16, E4M3, QKV_ROPE, RESID, STORE_F32, SWIGLU, library_host
 
 pytestmark = pytest.mark.gpu
 
@@ -67,7 +69,7 @@ def test_large_tile_gemm_edges(cfg, tokens, requests):
     """256-row tiles: K splits of one and of odd numbers of slices (515 and
     2,050 rows; 620 requests give the head's K split one slice each), the
     unsplit RoPE epilogue with prompts that start anywhere in the tile's
-    four-row groups, a ragged last row tile and a K-split last round (16,500
+    four-row groups, more tiles than CUs and a ragged last row tile (16,500
     rows).  Tolerance: the repository's bounds for bf16 and e4m3 layers."""
     r = np.random.default_rng(tokens)
     cut = np.sort(r.choice(np.arange(1, tokens), requests - 1, replace=False))
@@ -76,6 +78,29 @@ def test_large_tile_gemm_edges(cfg, tokens, requests):
     say(f"case: 256-row tiles, cfg {cfg}, {tokens} tokens in {requests} requests (longest {lens.max()}), 1 step")
     case = make_case(cfg, lens=lens, shape=shape, n_req=requests)
     sample = sorted({0, int(lens.argmax()), requests // 3, requests // 2, requests - 1})
+    _against_oracle(case, sample, TOL_HDRAFT[case.fmt], TOL_Z[case.fmt])
+
+
+@pytest.mark.parametrize("cfg", [1, 4], ids=["bf16", "e4m3"])
+@pytest.mark.parametrize("tokens", [16385, 16500])
+def test_k_split_last_round_of_large_tiles(cfg, tokens):
+    """The last tiles of a large GEMM as K splits into blocks of their own, and
+    their reduce (residual, fp32 and SwiGLU outputs): the last row tile, of
+    one and of 116 rows.  Tolerance: the repository's bounds for bf16 and e4m3
+    layers."""
+    fmt = BF16 if cfg == 1 else E4M3
+    d = ffn = 1024
+    for epi, n, k, tail, splits in ((STORE_F32, d, 3 * d, 4, 12), (RESID, d, d, 4, 4), (SWIGLU, 2 * ffn, d, 8, 4),
+                                    (RESID, d, ffn, 4, 4)):
+        assert library_host().splits(fmt, epi, tokens, n, k) == 1
+        assert library_host().workspace_bytes(fmt, epi, tokens, n, k, 1 << 26) == tail * splits * 256 * 256 * 4
+    r = np.random.default_rng(tokens)
+    cut = np.sort(r.choice(np.arange(1, tokens - 60), 200, replace=False))
+    lens = np.diff(np.concatenate([[0], cut, [tokens]]))
+    say(f"case: K-split last round, cfg {cfg}, {tokens} tokens in {len(lens)} requests (longest {lens.max()}), 1 step")
+    case = make_case(cfg, lens=lens, shape=reduced_shape(d=d, n_q=8, n_kv=2, ffn=ffn, head_hidden=256), n_req=len(lens))
+    starts = np.concatenate([[0], cut])
+    sample = sorted({0, len(lens) // 2} | set(np.nonzero(starts + lens > 16384)[0].tolist()))
     _against_oracle(case, sample, TOL_HDRAFT[case.fmt], TOL_Z[case.fmt])
 
 
@@ -91,6 +116,59 @@ def test_few_row_gemm_edges(cfg, rows):
     say(f"case: few rows, cfg {cfg}, {rows} requests, d=2048, 2 steps")
     case = make_case(cfg, lens=[1] * rows, shape=shape, n_req=rows)
     _against_oracle(case, sorted({0, rows // 2, rows - 1}), TOL_HDRAFT[case.fmt], TOL_Z[case.fmt], steps=2)
+
+
+@pytest.mark.parametrize("cfg,d", [(1, 1024), (1, 2048), (4, 1024)], ids=["bf16 d=1024", "bf16 d=2048", "e4m3 d=1024"])
+@pytest.mark.parametrize("rows", [1, 33])
+def test_few_row_gated_qkv(cfg, d, rows):
+    """A gated q|k|v narrow enough for the few-row kernel, unsplit: the gate
+    columns of its RoPE epilogue.  Tolerance: the repository's bounds for bf16
+    and e4m3 layers."""
+    fmt, columns = (BF16 if cfg == 1 else E4M3), (2 * 16 + 2 * 4) * 128
+    assert library_host().streams(fmt, QKV_ROPE, rows, columns, d)
+    assert library_host().splits(fmt, QKV_ROPE, rows, columns, d) == 1
+    shape = reduced_shape(d=d, n_q=16, n_kv=4, ffn=1024, head_hidden=256)
+    say(f"case: few rows, gated QKV, cfg {cfg}, d={d}, {rows} requests, 2 steps")
+    case = make_case(cfg, lens=[1] * rows, shape=shape, n_req=rows, attn_gate=True)
+    _against_oracle(case, sorted({0, rows // 2, rows - 1}), TOL_HDRAFT[case.fmt], TOL_Z[case.fmt], steps=2)
+
+
+@pytest.mark.parametrize("cfg", [1, 4], ids=["bf16", "e4m3"])
+@pytest.mark.parametrize("requests", [3, 20, 61])
+def test_few_row_results_and_the_rows_beside(cfg, requests):
+    """Calls of up to 64 rows on the few-row kernel, in another order of
+    requests: the same bits (rows of a call do not meet in any sum).  One
+    request alone may take other K splits and page ranges, so it agrees to the
+    spread of fp32 summation order (TOL_VARIANT)."""
+    shape = reduced_shape(d=2048, n_q=16, n_kv=4, ffn=2688, head_hidden=1024)
+    r = np.random.default_rng(requests)
+    lens = np.ones(requests, np.int32)
+    lens[r.integers(0, requests, min(3, 64 - requests))] += 1
+    say(f"case: few rows, cfg {cfg}, {requests} requests ({lens.sum()} rows) permuted and alone")
+    case = make_case(cfg, lens=lens, shape=shape, n_req=requests)
+    pred = make_predictor(case, max_slots=2 * requests + 1)
+    off = np.concatenate([[0], np.cumsum(lens)])
+    H, S = device_states(case), device_states(case, step_inputs(case, 1))
+
+    def calls(slots, order):
+        rows = np.concatenate([np.arange(off[i], off[i + 1]) for i in order])
+        z0, h0 = pred.prefill(slots, lens[order], *[x[rows].contiguous() for x in H], want_hdraft=True)
+        z1, h1 = pred.step(slots, *[x[order].contiguous() for x in S], want_hdraft=True)
+        z0, h0, z1, h1 = (tensor_to_f64(x) for x in (z0, h0, z1, h1))
+        at = np.concatenate([[0], np.cumsum(lens[order])])
+        return {i: (z0[k], z1[k], h0[at[k]:at[k + 1]], h1[k]) for k, i in enumerate(order)}
+
+    base = calls(list(range(requests)), list(range(requests)))
+    perm = calls(list(range(requests, 2 * requests)), r.permutation(requests).tolist())
+    for i in range(requests):
+        assert all(np.array_equal(a, b) for a, b in zip(base[i], perm[i])), i
+    pred.release(list(range(2 * requests)))
+    for i in sorted({0, requests // 2, requests - 1}):
+        alone = calls([2 * requests], [i])[i]
+        pred.release([2 * requests])
+        assert z_errors(np.array(alone[:2]), np.array(base[i][:2])).max() <= TOL_VARIANT, i
+        assert rel_fro(alone[2], base[i][2]) <= TOL_VARIANT and rel_fro(alone[3], base[i][3]) <= TOL_VARIANT, i
+    pred.close()
 
 
 @pytest.mark.parametrize("cfg", [1, 4], ids=["bf16", "e4m3"])

@@ -107,8 +107,8 @@ __device__ __forceinline__ float4 rowsum_load(const RowSum& rs, int64_t row, int
 // and every access is a 16-byte (x, y2) or 8-byte (bf16 y, gamma) access
 // with consecutive threads on consecutive addresses.
 // With SUM the row is a RowSum's (a split-K GEMM finished here) instead of x.
-// NT is 256 for many rows; up to one block per CU each takes the whole CU's
-// issue width instead (NT up to 1,024, see launch_rmsnorm_sum).
+// NT is 256 for many rows; up to two rows per CU a block takes a row with up
+// to 1,024 threads (see launch_rmsnorm_sum).
 template <typename TY, typename TG, int V, bool SUM = false, int NT = 256>
 __global__ void __launch_bounds__(NT)
 rmsnorm_vec_kernel(int d, const float* x, int64_t ldx, const TG* gamma, float eps, TY* y,
@@ -678,13 +678,13 @@ bool rowsum_supported(int d) { return d == 1024 || d == 2048 || d == 4096 || d =
 void launch_rmsnorm_sum(int act_fmt, int gamma_fmt, int rows, int d, const RowSum& rs, const void* gamma,
                         float eps, void* y, int64_t ldy, hipStream_t st, const MetaFetch& mf) {
     if (rows <= 0) return;
-    // Up to 512 rows (two per CU) a wide block per row (d / 4 threads, at
+    // Up to two rows per CU a wide block per row (d / 4 threads, at
     // most 1,024) hides the partials' latency better than 256 threads of d /
     // 1024 groups each; with more rows the narrow blocks fill the chip.
     // Measured at d = 4096 (narrow / wide, us): 1 row of 16 splits 18.7 /
     // 7.7, 130 rows of 8 12.0 / 6.9, 512 rows of 4 10.6 / 10.1; 777 rows of 4
     // narrow 13.4 (6 TB/s).
-    const bool wide = rows <= 512;
+    const bool wide = rows <= 2 * gemm_device_cus();
     const dim3 grid(rows + mf.blocks);
 #define OUTLETS_NORMS_L(TY, TG, VV, NT)                                                                    \
     hipLaunchKernelGGL((rmsnorm_vec_kernel<TY, TG, VV, true, NT>), grid, dim3(NT), 0, st, d, nullptr, 0,   \
@@ -837,7 +837,7 @@ bool launch_norm_pool_prefill(int act_fmt, int gamma_fmt, int n_req, int n_tiles
     // 4096 with the second stage (one group / four, us): 25 tiles 34.9 / 21.7,
     // 186 35.3 / 24.9, 400 53.2 / 54.9, 854 108.3 / 113.2.  (d = 8192: two
     // groups; four of its 8 float4 per thread would spill.)
-    const bool few = n_tiles <= 256;
+    const bool few = n_tiles <= gemm_device_cus();
 #define OUTLETS_NP_V(TY, TG, VV)                                                                        \
     case VV:                                                                                            \
         if (few)                                                                                        \

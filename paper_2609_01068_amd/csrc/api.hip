@@ -327,7 +327,7 @@ LayerGemms layer_gemms(const outlets_ctx* c, const CallBufs& b, const void* hl, 
     g.b_gu.p[1] = w.w_up;
     g.b_gu.scale[1] = static_cast<const uint16_t*>(w.s_up);
     if (c->w_fmt == FMT_F32) {
-        g.n_gu = c->F;            // dual-row VALU kernel
+        g.n_gu = c->F;            // a gate row and an up row per output
     } else {
         g.b_gu.paired = 1;        // 32-row gate/up interleave
         g.n_gu = 2 * c->F;
@@ -342,13 +342,12 @@ LayerGemms layer_gemms(const outlets_ctx* c, const CallBufs& b, const void* hl, 
     return g;
 }
 
-// Draft model head input: the newest token's h_draft is the second half of
-// each pooled row ([mean ; newest]); bf16 weights read its hi/lo split.
-// K splits of the head GEMM over `rows` A rows: kHeadSplits, doubled up to
-// 32 while the workgroups fill at most half the CUs and every split keeps at
-// least 4 K slices of 64 (the fp32 path keeps kHeadSplits).  Measured: 32
-// splits for 64 rows take the head from 0.033 to 0.024 ms; 16 instead of 8
-// for 1,024 rows is slower (the finish reads twice the partials).
+// K splits of the head GEMM over `rows` A rows: kHeadSplits on the few-row
+// kernel (up to 64 rows, see gemm_streams) and with fp32 weights; on the tiles
+// doubled up to 32 while the workgroups fill at most half the CUs and every
+// split keeps at least 4 K slices of 64.  Measured there: 32 splits for 64
+// rows took the head from 0.033 to 0.024 ms; 16 instead of 8 for 1,024 rows is
+// slower (the finish reads twice the partials).
 int head_splits(const outlets_ctx* c, int rows) {
     int s = kHeadSplits;
     if (c->w_fmt == FMT_F32 || gemm_streams(FMT_BF16, EPI_PARTIAL, rows, static_cast<int>(c->H1), static_cast<int>(2 * c->d))) return s;
@@ -358,6 +357,8 @@ int head_splits(const outlets_ctx* c, int rows) {
     return s;
 }
 
+// Draft model head input: the newest token's h_draft is the second half of
+// each pooled row ([mean ; newest]); bf16 weights read its hi/lo split.
 GemmA lm_input(const outlets_ctx* c) {
     return (c->w_fmt == FMT_F32) ? gemm_a(c->cb.pooled + c->d, 2 * c->d, c->d)
                                  : gemm_a(c->cb.pooled_bf16 + c->d, 2 * c->d, c->d);
@@ -1038,8 +1039,8 @@ int outlets_predict_step_noalloc(outlets_ctx* ctx, int32_t n_req, const int32_t*
 // target-model hidden state (no draft layer), with its own weights and
 // per-slot running sums.
 
-// Stage int32 metadata through the pinned double buffer into probe_meta (the
-// a copy kernel: no copy-engine transfer to wait on).
+// Stage int32 metadata through the pinned double buffer into probe_meta (by a
+// copy kernel: no copy-engine transfer to wait on).
 int upload_probe_meta(outlets_ctx* c, const std::vector<int32_t>& v, hipStream_t st) {
     if (static_cast<int64_t>(v.size()) > c->cb.meta_cap) return fail(OUTLETS_ERR_INVALID_ARG, "call metadata exceeds capacity");
     const int s = c->stage;

@@ -444,8 +444,7 @@ __device__ __forceinline__ void gemm_epilogue_pairs(f32x4 (&acc)[8][4], int M, c
     constexpr int BM = 256, BN = 256, FM = 8;
     const int lane = threadIdx.x & 63, grp = lane >> 4, l16 = lane & 15;
     auto pack = [](float lo, float hi) { return f32_to_bf16(lo) | (uint32_t(f32_to_bf16(hi)) << 16); };
-    // e4m3: the row scales of the lane's four columns (columns of half h at
-    // hcol[h], + 1)
+    // e4m3: the row scales of columns n and n + 1
     auto scales = [&](int n, float& s0, float& s1) {
         s0 = s1 = 1.f;
         if (E4M3) {
@@ -847,7 +846,7 @@ gemm_mfma_256x256(int M, int N, int K, GemmA A, GemmB B, GemmC C, int k_per_spli
 }
 
 // ---------------------------------------------------------------- few rows
-// Calls of at most 16 MB activation rows stream the weights: each is
+// Calls of at most 64 rows (MB blocks of 16) stream the weights: each is
 // multiplied once per 16 rows and not needed again.  Weights go from HBM
 // straight into MFMA operands; activations, which every wave needs, go
 // through LDS.  A workgroup takes 16 RB NW weight rows on NW x KW waves (NW
@@ -1616,8 +1615,8 @@ void launch_f32(int M, int N, int K, const GemmA& a, const GemmB& b, const GemmC
 // 79.2).  Measured against 64 x
 // 256 tiles with their reduces (d = 4096 bf16, 16 / 64 rows, us): fused
 // projection 25.0 / 29.3 -> 21.3 / 27.0, QKV 20.6 / 25.9 -> 19.3 / 24.0, O 13.9 /
-// 17.8 -> 10.2 / 13.2, down 25.3 / 31.5 -> 23.9 / 31.6, length head 17.1 / 18.3 ->
-// 12.5 / 19.7, the two norms and the pooling (fewer partials to add) 26.0 /
+// 17.8 -> 10.2 / 13.2, down 25.3 / 31.5 -> 23.9 / 31.6, length head with
+// its finish 16.4 / 17.9 -> 11.7 / 13.8, the two norms and the pooling (fewer partials to add) 26.0 /
 // 26.7 -> 15.5 / 16.3; gate/up 45.0 / 48.0 -> 46.9 / 60.1; d = 8192 e4m3, 16 / 32
 // rows: fused 72.5 / 75.4 -> 42.6 / 49.1, gate/up 174 / 171 -> 108 / 118, down 70.1 /
 // 72.0 -> 46.7 / 53.8.  Matrices below 4M weights take about 1 us to read:

@@ -1090,7 +1090,7 @@ gemm_stream(int M, int N, int K, GemmA A, GemmB B, GemmC C, int k_per_split) {
 // one split at a time (us): tile_reduce of 128 tiles x 2 splits 39 -> 20
 // (residual), 29 -> 15 (fp32), of 80 SwiGLU tiles x 3 19 -> 11; splitk_reduce of
 // 777 x 4,096 x 4 splits 19.5 -> 13.6, of 1,081 x 8,192 x 3 50 -> 29; the RoPE
-// reduce, half of whose time is V's 2-byte stores, 15.4 -> 13.6 (512 tokens).
+// reduce, half of whose time is V's 2-byte stores, 15.4 -> 12.2 (512 tokens).
 
 // Four columns of S partials `stride` floats apart, added in split order.
 __device__ __forceinline__ f32x4 sum_splits(const float* p, int64_t stride, int S) {

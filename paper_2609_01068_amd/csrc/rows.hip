@@ -19,7 +19,7 @@ namespace {
 // would have to be waited on by the compute queue, and a kernel of its own
 // waited for the host link with the chip idle (one request with a 777-token
 // prompt, prefill and 8 steps at the 8B widths: 1,878 us a kernel of its own,
-// 1,833 beside the norm; 512-request step 1,831 / 1,804).  `host` is read with
+// 1,833 beside the norm; a 512-request step does not show it).  `host` is read with
 // vector loads (it is not restrict-qualified, and the index differs by lane
 // or wave), so nothing of it is kept in the scalar cache.  One wave per
 // request: each wave's reads cross the link again, and a block per request

@@ -2,6 +2,7 @@
 computes them (256 compute units where there is no device)."""
 import ctypes as C
 import functools
+import os
 
 import pytest
 
@@ -14,6 +15,8 @@ WIDTHS = [n for n in range(512, 16385, 256)]
 
 @functools.lru_cache(maxsize=None)
 def library_host():
+    if not os.path.exists(build.LIB_PATH):
+        build.build(verbose=False)
     lib = C.CDLL(build.LIB_PATH)
 
     def function(name, params, result=C.c_int):
